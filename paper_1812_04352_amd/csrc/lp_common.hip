@@ -75,14 +75,81 @@ unsigned grid_for(size_t work) {
 
 // ---------------------------------------------------------------- opening layer
 
+// u0[e][r] = sigma(sum_f L[r][f] y[e][f]), f in order. A workgroup owns a tile of
+// OE examples x OR rows; both operands pass through LDS in pieces of OF features
+// (coalesced loads, the next piece requested before the current one is used), and
+// a thread sums a 2 x 2 patch of the tile from 16-byte LDS reads (row pitch OF + 4
+// words: the 16 rows of a read start 4 banks apart). One thread per output, its
+// two rows read from global memory feature by feature, measured 122 us for
+// 16384 x 128 -> 32 fp32 (bound by uncoalesced reads and a serial chain of loads).
+constexpr int OE = 32, OR = 32;
+template <typename T> constexpr int OF = 512 / (int)sizeof(T);  // 512-byte pieces of a row
+
 template <typename T, int ACT>
 __global__ __launch_bounds__(NT) void k_open_dense(const T* y, const T* L, T* u0, int B, int q, int nf) {
-  const size_t tot = (size_t)B * q;
-  for (size_t i = (size_t)blockIdx.x * NT + threadIdx.x; i < tot; i += (size_t)gridDim.x * NT) {
-    const size_t e = i / q, r = i - e * q;
-    T acc = T(0);
-    for (int f = 0; f < nf; ++f) acc = fma(L[r * nf + f], y[e * nf + f], acc);
-    u0[i] = act_f<T, ACT>(acc);
+  constexpr int F = OF<T>, LD = F + 16 / (int)sizeof(T), NLD = (OE + OR) * F / NT;
+  __shared__ __align__(16) T sh[(OE + OR) * LD];
+  const int e0 = blockIdx.x * OE, r0 = blockIdx.y * OR, t = threadIdx.x;
+  // piece f0: rows 0 .. OE-1 of sh are the examples, the rest the weight rows; zero outside
+  T reg[NLD];
+  auto fetch = [&](int f0) {
+#pragma unroll
+    for (int k = 0; k < NLD; ++k) {
+      const int i = t + k * NT, row = i / F, f = f0 + i % F;
+      const bool in = f < nf && (row < OE ? e0 + row < B : r0 + row - OE < q);
+      const T* p = row < OE ? y + (size_t)(e0 + row) * nf : L + (size_t)(r0 + row - OE) * nf;
+      reg[k] = in ? p[f] : T(0);
+    }
+  };
+  const int te = t % 16, tr = t / 16;
+  T acc[2][2] = {{T(0), T(0)}, {T(0), T(0)}};
+  fetch(0);
+  for (int f0 = 0; f0 < nf; f0 += F) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NLD; ++k) {
+      const int i = t + k * NT;
+      sh[(i / F) * LD + i % F] = reg[k];
+    }
+    __syncthreads();
+    if (f0 + F < nf) fetch(f0 + F);
+    using V = typename Vec16<T>::type;
+    constexpr int nv = Vec16<T>::n;
+    const int nn = (min(F, nf - f0) + nv - 1) / nv;  // past nf both operands are zero
+#pragma unroll 4
+    for (int v = 0; v < nn; ++v) {
+      V a[2], b[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        a[i] = *reinterpret_cast<const V*>(sh + (te + 16 * i) * LD + nv * v);
+        b[i] = *reinterpret_cast<const V*>(sh + (OE + tr + 16 * i) * LD + nv * v);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          if constexpr (nv == 4) {
+            acc[i][j] = fma(b[j].x, a[i].x, acc[i][j]);
+            acc[i][j] = fma(b[j].y, a[i].y, acc[i][j]);
+            acc[i][j] = fma(b[j].z, a[i].z, acc[i][j]);
+            acc[i][j] = fma(b[j].w, a[i].w, acc[i][j]);
+          } else {
+            acc[i][j] = fma(b[j].x, a[i].x, acc[i][j]);
+            acc[i][j] = fma(b[j].y, a[i].y, acc[i][j]);
+          }
+        }
+    }
+  }
+  // through LDS, so that the output rows are written in order
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) sh[(te + 16 * i) * (OR + 1) + tr + 16 * j] = act_f<T, ACT>(acc[i][j]);
+  __syncthreads();
+  for (int i = t; i < OE * OR; i += NT) {
+    const int e = i / OR, r = i % OR;
+    if (e0 + e < B && r0 + r < q) u0[(size_t)(e0 + e) * q + r0 + r] = sh[e * (OR + 1) + r];
   }
 }
 
@@ -110,71 +177,192 @@ __global__ __launch_bounds__(NT) void k_open_conv(const T* y, const T* L, T* u0,
   }
 }
 
-// dL[r][f] = sum_e sigma'(z_er) lam0[e][r] y[e][f]; one workgroup per row r,
-// examples in order, z recomputed once per (e, r).
-template <typename T, int ACT>
-__global__ __launch_bounds__(NT) void k_open_grad_dense(const T* y, const T* L, const T* lam0, T* dL,
-                                                        int B, int q, int nf) {
-  __shared__ T sv[NT];
-  const int r = blockIdx.x;
-  // each thread owns features f = threadIdx.x + k*NT
-  T acc[4] = {T(0), T(0), T(0), T(0)};  // nf <= 4*NT
-  for (int e0 = 0; e0 < B; e0 += NT) {
-    const int e = e0 + threadIdx.x;
-    T s = T(0);
-    if (e < B) {
-      T z = T(0);
-      for (int f = 0; f < nf; ++f) z = fma(L[(size_t)r * nf + f], y[(size_t)e * nf + f], z);
-      s = dact_f<T, ACT>(z) * lam0[(size_t)e * q + r];
-    }
-    sv[threadIdx.x] = s;
-    __syncthreads();
-    const int ne = min(NT, B - e0);
-    for (int k = 0; k < 4; ++k) {
-      const int f = threadIdx.x + k * NT;
-      if (f < nf)
-        for (int t = 0; t < ne; ++t) acc[k] = fma(sv[t], y[(size_t)(e0 + t) * nf + f], acc[k]);
-    }
-    __syncthreads();
-  }
-  for (int k = 0; k < 4; ++k) {
-    const int f = threadIdx.x + k * NT;
-    if (f < nf) dL[(size_t)r * nf + f] = acc[k];
+// dL[r][f] = sum_e sigma'(z_er) lam0[e][r] y[e][f]; one workgroup of 16 waves per
+// row r (there is no workspace to combine several in). Lane l of a wave holds the
+// features l, l + 64, ... of GE examples at a time, read once, coalesced, straight
+// into registers, the next GE requested before the current ones are used; the
+// waves run without barriers. The GE values of z are added over the lanes in one
+// butterfly that halves their number per exchange, so that sigma' runs once for
+// all of them, and come back as scalars. fp32 sums over GE examples, then fp64 in
+// a fixed order. Bound by the one CU's reads of y: 16384 x 128 fp32, 32 rows:
+// 1776 us with a barrier and a chain of loads per 256 examples, 340 us
+// now.
+constexpr int GNT = 1024, GWAVES = GNT / 64;
+
+template <typename T>
+__device__ __forceinline__ T lane_value(T v, int lane) {
+  if constexpr (sizeof(T) == 4) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+  } else {
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)b >> 32), lane);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
   }
 }
 
-// dL[co][0][ty][tx] = sum_e sum_p sigma'(z[e,co,p]) lam0[e,co,p] y[e, p + t]: one
-// workgroup per output channel; thread t accumulates over pixels t, t+NT, ... of
-// every example for all 9 taps, then a fixed-order tree combines the threads.
-template <typename T, int ACT>
-__global__ __launch_bounds__(NT) void k_open_grad_conv(const T* y, const T* L, const T* lam0, T* dL,
-                                                       int B, int C, int H, int W) {
-  __shared__ double sh[NT];
-  const int co = blockIdx.x;
-  T acc[9];
-  for (int t = 0; t < 9; ++t) acc[t] = T(0);
-  const int P = H * W;
-  for (int e = 0; e < B; ++e) {
-    const T* ye = y + (size_t)e * P;
-    for (int p = threadIdx.x; p < P; p += NT) {
-      const int yy = p / W, x = p - yy * W;
-      T win[9];
-      T z = T(0);
-      for (int ty = 0; ty < 3; ++ty)
-        for (int tx = 0; tx < 3; ++tx) {
-          const int sy = yy + ty - 1, sx = x + tx - 1;
-          T v = (sy >= 0 && sy < H && sx >= 0 && sx < W) ? ye[sy * W + sx] : T(0);
-          win[ty * 3 + tx] = v;
-          z = fma(L[co * 9 + ty * 3 + tx], v, z);
-        }
-      const T s = dact_f<T, ACT>(z) * lam0[((size_t)e * C + co) * P + p];
-      for (int t = 0; t < 9; ++t) acc[t] = fma(s, win[t], acc[t]);
+// FPL features per lane, GE examples (a power of two <= 8) in flight
+template <typename T, int ACT, int FPL, int GE>
+__global__ __launch_bounds__(GNT) void k_open_grad_dense(const T* y, const T* L, const T* lam0, T* dL,
+                                                         int B, int q, int nf) {
+  __shared__ double sh[GWAVES][64];
+  const int r = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int LG = GE == 8 ? 3 : GE == 4 ? 2 : GE == 2 ? 1 : 0;
+  T w[FPL];
+  double acc[FPL];
+#pragma unroll
+  for (int k = 0; k < FPL; ++k) {
+    const int f = lane + 64 * k;
+    w[k] = f < nf ? L[(size_t)r * nf + f] : T(0);
+    acc[k] = 0.0;
+  }
+  T yn[GE][FPL], ln;
+  const int me = lane >> (6 - LG);  // the example whose z this lane ends up with
+  auto fetch = [&](int e0) {
+#pragma unroll
+    for (int i = 0; i < GE; ++i)
+#pragma unroll
+      for (int k = 0; k < FPL; ++k) {
+        const int f = lane + 64 * k;
+        yn[i][k] = e0 + i < B && f < nf ? y[(size_t)(e0 + i) * nf + f] : T(0);
+      }
+    ln = e0 + me < B ? lam0[(size_t)(e0 + me) * q + r] : T(0);
+  };
+  fetch(wave * GE);
+  for (int e0 = wave * GE; e0 < B; e0 += GWAVES * GE) {
+    T v[GE][FPL], p[GE];
+    const T lam = ln;
+#pragma unroll
+    for (int i = 0; i < GE; ++i) {
+      p[i] = T(0);
+#pragma unroll
+      for (int k = 0; k < FPL; ++k) {
+        v[i][k] = yn[i][k];
+        p[i] = fma(w[k], v[i][k], p[i]);
+      }
+    }
+    fetch(e0 + GWAVES * GE);
+    int off = 32;
+#pragma unroll
+    for (int n = GE; n > 1; n /= 2, off /= 2) {
+      const bool up = lane & off;
+#pragma unroll
+      for (int i = 0; i < n / 2; ++i) {
+        const T send = up ? p[i] : p[i + n / 2], keep = up ? p[i + n / 2] : p[i];
+        p[i] = keep + __shfl_xor(send, off, 64);
+      }
+    }
+    for (; off > 0; off /= 2) p[0] += __shfl_xor(p[0], off, 64);
+    const T s = e0 + me < B ? dact_f<T, ACT>(p[0]) * lam : T(0);
+    T a[FPL];
+#pragma unroll
+    for (int i = 0; i < GE; ++i) {
+      const T si = lane_value(s, i << (6 - LG));
+#pragma unroll
+      for (int k = 0; k < FPL; ++k) a[k] = i == 0 ? si * v[i][k] : fma(si, v[i][k], a[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < FPL; ++k) acc[k] += (double)a[k];
+  }
+#pragma unroll
+  for (int k = 0; k < FPL; ++k) {
+    __syncthreads();
+    sh[wave][lane] = acc[k];
+    __syncthreads();
+    const int f = lane + 64 * k;
+    if (wave == 0 && f < nf) {
+      double t = 0.0;
+      for (int j = 0; j < GWAVES; ++j) t += sh[j][lane];
+      dL[(size_t)r * nf + f] = (T)t;
     }
   }
-  for (int t = 0; t < 9; ++t) {
-    double v = block_sum<NT>((double)acc[t], sh);
-    if (threadIdx.x == 0) dL[co * 9 + t] = (T)v;
+}
+
+template <typename T, int ACT>
+void open_grad_dense(const T* y, const T* L, const T* lam0, T* dL, int B, int q, int nf, hipStream_t st) {
+  // about 64 registers of examples in flight per lane
+  const auto run = [&](auto fpl) {
+    constexpr int FPL = decltype(fpl)::value, W = FPL * (int)sizeof(T) / 4;
+    constexpr int GE = W <= 4 ? 8 : W <= 8 ? 4 : W <= 16 ? 2 : 1;
+    k_open_grad_dense<T, ACT, FPL, GE><<<q, GNT, 0, st>>>(y, L, lam0, dL, B, q, nf);
+  };
+  if (nf <= 64) run(std::integral_constant<int, 1>{});
+  else if (nf <= 128) run(std::integral_constant<int, 2>{});
+  else if (nf <= 256) run(std::integral_constant<int, 4>{});
+  else if (nf <= 512) run(std::integral_constant<int, 8>{});
+  else run(std::integral_constant<int, 16>{});
+}
+
+// dL[co][0][ty][tx] = sum_e sum_p sigma'(z[e,co,p]) lam0[e,co,p] y[e, p + t]: one
+// workgroup of 1024 threads per weight (co, ty, tx) (there is no workspace to
+// combine several in). Each recomputes its channel's z, so its work is that of the
+// window reads and the activation. Groups of IM images (IM P <= OCP GNT pixels)
+// pass through LDS with a zero halo, the next group's values requested before the
+// current one is used; a thread's pixels lie at the same offsets in every group.
+// fp32 sums over a thread's pixels of one group, then fp64 in a fixed order.
+// 500 images of 28 x 28: 2245 us with one workgroup per channel and one pixel per
+// thread straight from memory (a chain of loads), 179 us now.
+constexpr int OCP = 8;             // pixels per thread and group
+constexpr int OC_LDS = 12 * 1024;  // floats of the haloed group
+
+template <int ACT>
+__global__ __launch_bounds__(GNT) void k_open_grad_conv(const float* y, const float* L, const float* lam0, float* dL,
+                                                        int B, int C, int H, int W, int IM) {
+  __shared__ float img[OC_LDS];
+  __shared__ double sh[GNT];
+  const int co = blockIdx.x / 9, tap = blockIdx.x % 9, t = threadIdx.x;
+  const int P = H * W, PW = W + 2, PH = (H + 2) * PW;
+  float w[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) w[k] = L[co * 9 + k];
+  for (int i = t; i < IM * PH; i += GNT) img[i] = 0.f;
+  int at[OCP], gl[OCP], im[OCP];  // window corner in img, offset in lam0, image of the group
+#pragma unroll
+  for (int k = 0; k < OCP; ++k) {
+    const int i = t + k * GNT, p = i % P, yy = p / W;
+    im[k] = i / P;
+    if (im[k] >= IM) im[k] = B;  // none
+    at[k] = i / P * PH + yy * PW + (p - yy * W);
+    gl[k] = (i / P * C + co) * P + p;
   }
+  const int toff = tap / 3 * PW + tap % 3;
+  float yv[OCP], lv[OCP];
+  auto fetch = [&](int e0) {
+    const float* ye = y + (size_t)e0 * P;
+    const float* le = lam0 + (size_t)e0 * C * P;
+#pragma unroll
+    for (int k = 0; k < OCP; ++k) {
+      const bool in = e0 + im[k] < B;
+      yv[k] = in ? ye[t + k * GNT] : 0.f;
+      lv[k] = in ? le[gl[k]] : 0.f;
+    }
+  };
+  fetch(0);
+  double acc = 0.0;
+  for (int e0 = 0; e0 < B; e0 += IM) {
+    float lam[OCP];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < OCP; ++k) {
+      lam[k] = lv[k];
+      if (im[k] < IM) img[at[k] + PW + 1] = yv[k];
+    }
+    __syncthreads();
+    if (e0 + IM < B) fetch(e0 + IM);
+    float a = 0.f;
+#pragma unroll
+    for (int k = 0; k < OCP; ++k) {
+      if (e0 + im[k] >= B) continue;
+      const float* q = img + at[k];
+      float z = 0.f;
+#pragma unroll
+      for (int j = 0; j < 9; ++j) z = fma(w[j], q[j / 3 * PW + j % 3], z);
+      a = fma(dact_f<float, ACT>(z) * lam[k], q[toff], a);
+    }
+    acc += (double)a;
+  }
+  const double v = block_sum<GNT>(acc, sh);
+  if (t == 0) dL[co * 9 + tap] = (float)v;
 }
 
 template <typename T>
@@ -208,7 +396,8 @@ hipError_t open_fwd_t(const Shape& s, int opening, int nf, int B, const void* y,
   return with_act<T>(s.act, [&](auto ac) -> hipError_t {
     constexpr int ACT = decltype(ac)::value;
     if (opening == 1)
-      k_open_dense<T, ACT><<<grid_for((size_t)B * q), NT, 0, st>>>((const T*)y, (const T*)L, (T*)u0, B, q, nf);
+      k_open_dense<T, ACT><<<dim3((B + OE - 1) / OE, (q + OR - 1) / OR), NT, 0, st>>>((const T*)y, (const T*)L,
+                                                                                      (T*)u0, B, q, nf);
     else
       k_open_conv<T, ACT><<<grid_for((size_t)B * q), NT, 0, st>>>((const T*)y, (const T*)L, (T*)u0, B, s.C,
                                                                   s.H, s.W);
@@ -222,11 +411,16 @@ hipError_t open_grad_t(const Shape& s, int opening, int nf, int B, const void* y
   const int q = s.C * s.H * s.W;
   return with_act<T>(s.act, [&](auto ac) -> hipError_t {
     constexpr int ACT = decltype(ac)::value;
-    if (opening == 1)
-      k_open_grad_dense<T, ACT><<<q, NT, 0, st>>>((const T*)y, (const T*)L, (const T*)lam0, (T*)dL, B, q, nf);
-    else
-      k_open_grad_conv<T, ACT><<<s.C, NT, 0, st>>>((const T*)y, (const T*)L, (const T*)lam0, (T*)dL, B, s.C,
-                                                   s.H, s.W);
+    if (opening == 1) {
+      open_grad_dense<T, ACT>((const T*)y, (const T*)L, (const T*)lam0, (T*)dL, B, q, nf, st);
+    } else if constexpr (sizeof(T) == 4) {
+      const int IM = std::min(OCP * GNT / (s.H * s.W), OC_LDS / ((s.H + 2) * (s.W + 2)));
+      if (IM < 1) return hipErrorNotSupported;
+      k_open_grad_conv<ACT><<<s.C * 9, GNT, 0, st>>>((const float*)y, (const float*)L, (const float*)lam0, (float*)dL,
+                                                     B, s.C, s.H, s.W, IM);
+    } else {
+      return hipErrorNotSupported;
+    }
     return hipGetLastError();
   });
 }
