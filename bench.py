@@ -39,7 +39,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 PEAK_TFLOPS = {"f32": 157.3, "f64": 78.6}  # dense MFMA / fp32 vector (packed), fp64
 
-# dense fp32 widths the library runs on the matrix cores (the others on the vector ALUs)
+# dense fp32 widths whose kernels keep a sigma' record
 MATRIX_CORE_WIDTHS = (32, 64, 220)
 
 KIND_NAMES = ["fwd_fc", "fwd_fres", "fwd_corrf", "fwd_coarsest", "adj_fc", "adj_fres", "adj_corrf",
@@ -188,7 +188,8 @@ def kernel_model(wl, kind: str, fwd_iters: int, adj_iters: int, rec: int = 0, cp
 _FAMILY_SOURCES = {
     "lp::conv::": ["lp_conv.hip"],
     "lp::mfma::": ["lp_dense_mfma.hip"],
-    "lp::dense::": ["lp_dense_impl.h", "lp_dense_f32.hip", "lp_dense_f64.hip"],
+    "lp::dense::": ["lp_dense_impl.h", "lp_dense_f32.hip"],
+    "lp::narrow::": ["lp_dense_narrow.hip"],
     "lp::wide::": ["lp_dense_wide.hip"],
 }
 _SHARED_SOURCES = ["lp_internal.h", "lp_device.h"]
@@ -228,7 +229,7 @@ def kernel_kind(name: str):
     import re
     if "k_grad<" in name or "k_grad_partial<" in name:
         return "gradient"
-    m = re.search(r"lp::(mfma|conv|dense|wide)::k_(fwd|adj)(_sweep|_serial|_iv)?<([^>]*)>", name)
+    m = re.search(r"lp::(mfma|conv|dense|narrow|wide)::k_(fwd|adj)(_sweep|_serial|_iv)?<([^>]*)>", name)
     if not m:
         return None
     fam, d, suffix, targs = m.groups()
@@ -236,7 +237,7 @@ def kernel_kind(name: str):
     if suffix == "_serial":
         mode = 3
     else:
-        mode = int(args[{"mfma": 1, "conv": 0, "dense": 2, "wide": 1}[fam]])
+        mode = int(args[{"mfma": 1, "conv": 0, "dense": 2, "narrow": 2, "wide": 1}[fam]])
     return f"{d}_" + ["fc", "fres", "corrf", "coarsest"][mode]
 
 
@@ -494,8 +495,7 @@ def measure(wl, steps: int, warmup: int, no_record: bool = False, storage: str =
         roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s"}
     else:
         achieved = flops / launches / (avg_ms / 1e3) / 1e12
-        on_mfma = wl.dtype == "f32" and (wl.layer == "conv3x3" or wl.q in MATRIX_CORE_WIDTHS) and \
-            os.environ.get("LP_DENSE_PATH") != "valu"
+        on_mfma = os.environ.get("LP_DENSE_PATH") != "valu" or wl.dtype == "f64" or wl.q not in (32, 64)
         roof = {"bound": "mfma" if on_mfma else "alu", "achieved": achieved, "peak": PEAK_TFLOPS[wl.dtype],
                 "unit": "TFLOP/s"}
     roof["frac"] = achieved / roof["peak"]

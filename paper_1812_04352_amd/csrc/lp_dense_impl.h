@@ -11,7 +11,7 @@
 // The activation is a uniform runtime value; the dtype T and the width Q are
 // template parameters (the row lives in registers), and each sweep mode is its
 // own kernel symbol so profiles attribute time per mode.
-// Included once per dtype by lp_dense_f32.hip / lp_dense_f64.hip.
+// Included by lp_dense_f32.hip.
 #pragma once
 
 #include "lp_device.h"
@@ -677,44 +677,3 @@ hipError_t grad(const GradArgs& a, hipStream_t st) {
 
 }  // namespace dense
 }  // namespace lp
-
-// Defines the per-dtype entry points dense_*_SFX over the supported widths.
-#define LP_DENSE_DEFINE(T, SFX, WIDE)                                                                        \
-  namespace lp {                                                                                       \
-  hipError_t dense_sweep_##SFX(int q, int dir, const SweepArgs& a, hipStream_t st, int* partials) {    \
-    switch (q) {                                                                                       \
-      case 8: return dense::sweep<T, 8>(dir, a, st, partials);                                         \
-      case 16: return dense::sweep<T, 16>(dir, a, st, partials);                                       \
-      case 32: return dense::sweep<T, 32>(dir, a, st, partials);                                       \
-      case 64: if (WIDE) return dense::sweep<T, (WIDE ? 64 : 8)>(dir, a, st, partials); break;                                       \
-    }                                                                                                  \
-    return hipErrorNotSupported;                                                                       \
-  }                                                                                                    \
-  hipError_t dense_serial_##SFX(int q, int dir, const SerialArgs& a, hipStream_t st) {                 \
-    switch (q) {                                                                                       \
-      case 8: return dense::serial<T, 8>(dir, a, st);                                                  \
-      case 16: return dense::serial<T, 16>(dir, a, st);                                                \
-      case 32: return dense::serial<T, 32>(dir, a, st);                                                \
-      case 64: if (WIDE) return dense::serial<T, (WIDE ? 64 : 8)>(dir, a, st); break;                                                \
-    }                                                                                                  \
-    return hipErrorNotSupported;                                                                       \
-  }                                                                                                    \
-  hipError_t dense_resid_##SFX(int q, int dir, const ResidArgs& a, hipStream_t st, int* partials) {    \
-    switch (q) {                                                                                       \
-      case 8: return dense::resid<T, 8>(dir, a, st, partials);                                         \
-      case 16: return dense::resid<T, 16>(dir, a, st, partials);                                       \
-      case 32: return dense::resid<T, 32>(dir, a, st, partials);                                       \
-      case 64: if (WIDE) return dense::resid<T, (WIDE ? 64 : 8)>(dir, a, st, partials); break;                                       \
-    }                                                                                                  \
-    return hipErrorNotSupported;                                                                       \
-  }                                                                                                    \
-  hipError_t dense_grad_##SFX(int q, const GradArgs& a, hipStream_t st) {                              \
-    switch (q) {                                                                                       \
-      case 8: return dense::grad<T, 8>(a, st);                                                         \
-      case 16: return dense::grad<T, 16>(a, st);                                                       \
-      case 32: return dense::grad<T, 32>(a, st);                                                       \
-      case 64: if (WIDE) return dense::grad<T, (WIDE ? 64 : 8)>(a, st); break;                                                       \
-    }                                                                                                  \
-    return hipErrorNotSupported;                                                                       \
-  }                                                                                                    \
-  }

@@ -508,8 +508,6 @@ int mgrit_solve(const lp_problem* p, const lp_mgrit* m, int dir, const void* K, 
 
 namespace lp {
 
-bool dense_width_supported(int q) { return q == 8 || q == 16 || q == 32 || q == 64; }
-
 int dense_grad_chunks(int B, int N) {
   // enough workgroups to fill the chip when N is small, at least 64 and at most
   // 2048 examples per chunk: each of a chunk's four waves then sums at most 512
@@ -524,7 +522,8 @@ int dense_grad_chunks(int B, int N) {
 bool shape_supported(const Shape& s) {
   if (s.layer == 0)
     return s.H == 1 && s.W == 1 &&
-           ((dense_width_supported(s.C) && !(s.dtype == 1 && s.C > 32)) || (s.dtype == 0 && wide_width_supported(s.C)));
+           (narrow_supported(s.dtype, s.C) ||
+            (s.dtype == 0 && (mfma_width_supported(s.C) || wide_width_supported(s.C))));
   return conv_supported(s);
 }
 
@@ -565,27 +564,31 @@ hipError_t launch_sweep(const Shape& s, int dir, const SweepArgs& a, hipStream_t
   if (s.layer != 0) return conv_sweep(s, dir, a, st, partials);
   if (use_wide(s)) return wide_sweep(s.C, dir, a, st, partials);
   if (use_mfma(s)) return mfma_sweep(s.C, dir, a, st, partials);
-  return s.dtype == 0 ? dense_sweep_f32(s.C, dir, a, st, partials) : dense_sweep_f64(s.C, dir, a, st, partials);
+  if (narrow_supported(s.dtype, s.C)) return narrow_sweep(s.dtype, s.C, dir, a, st, partials);
+  return dense_sweep_f32(s.C, dir, a, st, partials);
 }
 
 hipError_t launch_serial(const Shape& s, int dir, const SerialArgs& a, hipStream_t st) {
   if (s.layer != 0) return conv_serial(s, dir, a, st);
   if (use_wide(s)) return wide_serial(s.C, dir, a, st);
   if (use_mfma(s)) return mfma_serial(s.C, dir, a, st);
-  return s.dtype == 0 ? dense_serial_f32(s.C, dir, a, st) : dense_serial_f64(s.C, dir, a, st);
+  if (narrow_supported(s.dtype, s.C)) return narrow_serial(s.dtype, s.C, dir, a, st);
+  return dense_serial_f32(s.C, dir, a, st);
 }
 
 hipError_t launch_resid(const Shape& s, int dir, const ResidArgs& a, hipStream_t st, int* partials) {
   if (s.layer != 0) return conv_resid(s, dir, a, st, partials);
   if (use_wide(s)) return wide_resid(s.C, dir, a, st, partials);
-  return s.dtype == 0 ? dense_resid_f32(s.C, dir, a, st, partials) : dense_resid_f64(s.C, dir, a, st, partials);
+  if (narrow_supported(s.dtype, s.C)) return narrow_resid(s.dtype, s.C, dir, a, st, partials);
+  return dense_resid_f32(s.C, dir, a, st, partials);
 }
 
 hipError_t launch_grad(const Shape& s, const GradArgs& a, hipStream_t st) {
   if (s.layer != 0) return conv_grad(s, a, st);
   if (use_wide(s)) return wide_grad(s.C, a, st);
   if (use_mfma(s)) return mfma_grad(s.C, a, st);
-  return s.dtype == 0 ? dense_grad_f32(s.C, a, st) : dense_grad_f64(s.C, a, st);
+  if (narrow_supported(s.dtype, s.C)) return narrow_grad(s.dtype, s.C, a, st);
+  return dense_grad_f32(s.C, a, st);
 }
 
 }  // namespace lp

@@ -139,15 +139,19 @@ int grad_partial_floats(const Shape& s);  // values per (layer, chunk) gradient 
 bool shape_supported(const Shape& s);
 int min_tile(const Shape& s);             // fewest examples any sweep/residual workgroup covers
 
-// Dense VALU family (lp_dense_impl.h, instantiated per dtype in lp_dense_f32.hip / lp_dense_f64.hip)
-#define LP_DENSE_DECL(SFX)                                                                          \
-  hipError_t dense_sweep_##SFX(int q, int dir, const SweepArgs& a, hipStream_t st, int* partials);  \
-  hipError_t dense_serial_##SFX(int q, int dir, const SerialArgs& a, hipStream_t st);               \
-  hipError_t dense_resid_##SFX(int q, int dir, const ResidArgs& a, hipStream_t st, int* partials);  \
-  hipError_t dense_grad_##SFX(int q, const GradArgs& a, hipStream_t st);
-LP_DENSE_DECL(f32)
-LP_DENSE_DECL(f64)
-bool dense_width_supported(int q);
+// Dense VALU family (lp_dense_impl.h, fp32 widths 32 and 64, lp_dense_f32.hip)
+hipError_t dense_sweep_f32(int q, int dir, const SweepArgs& a, hipStream_t st, int* partials);
+hipError_t dense_serial_f32(int q, int dir, const SerialArgs& a, hipStream_t st);
+hipError_t dense_resid_f32(int q, int dir, const ResidArgs& a, hipStream_t st, int* partials);
+hipError_t dense_grad_f32(int q, const GradArgs& a, hipStream_t st);
+
+// Dense matrix-core family of narrow layers (lp_dense_narrow.hip): fp32 widths 8 and
+// 16, fp64 widths 8, 16 and 32
+bool narrow_supported(int dtype, int q);
+hipError_t narrow_sweep(int dtype, int q, int dir, const SweepArgs& a, hipStream_t st, int* partials);
+hipError_t narrow_serial(int dtype, int q, int dir, const SerialArgs& a, hipStream_t st);
+hipError_t narrow_resid(int dtype, int q, int dir, const ResidArgs& a, hipStream_t st, int* partials);
+hipError_t narrow_grad(int dtype, int q, const GradArgs& a, hipStream_t st);
 
 // Dense fp32 matrix-core family (lp_dense_mfma.hip), widths 32 and 64
 bool mfma_width_supported(int q);
