@@ -23,7 +23,8 @@
 // examples. The earlier design (one thread per example, weights broadcast from
 // LDS) evaluated Q activations and Q^2 products per thread in a row: a serial
 // update of 1003 examples at width 16 in fp64 took 8.1 us per adjoint layer and
-// 3.2 us per forward layer, ADJ_US and FWD_US here.
+// 3.2 us per forward layer, 0.6 and 0.5 here; Peaks-shaped sweeps (2048 layers, 5000
+// examples, width 8): finest adjoint FC 251 -> 213 us, 4.6 TB/s.
 #include <algorithm>
 #include <type_traits>
 
@@ -37,6 +38,11 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int WAVES = 4;  // waves per sweep workgroup
+
+// Where 256 registers suffice, at least two waves per SIMD are asked for: the
+// compiler then keeps the accumulators in the vector registers proper instead of
+// moving them in and out of the accumulation registers around every product.
+#define LP_NARROW_WAVES(Q) __attribute__((amdgpu_waves_per_eu(Q <= 16 ? 2 : 1, 8)))
 
 template <typename T>
 struct Mx;
@@ -121,9 +127,9 @@ __device__ __forceinline__ void ld_tr(Wt<T, Q>& w, const T* __restrict__ Kn, int
     }
 }
 
-// z = init + A v
+// z[0 .. Q/4) = init + A v
 template <typename T, int Q>
-__device__ __forceinline__ void prod(T (&z)[Q / 4], const Wt<T, Q>& w, const T (&v)[Q / 4], const T (&init)[Q / 4]) {
+__device__ __forceinline__ void prod(T* z, const Wt<T, Q>& w, const T (&v)[Q / 4], const T (&init)[Q / 4]) {
   using D = Dim<Q>;
 #pragma unroll
   for (int mb = 0; mb < D::NB; ++mb) {
@@ -202,8 +208,8 @@ struct Step {
 // ------------------------------------------------------------------ sweeps
 // Workgroup (k, y): interval k, tiles of example block y; y is the fast index, so
 // workgroups in flight share an interval's weights in L1 and L2.
-template <typename T, int Q, int MODE, int ET>
-__global__ __launch_bounds__(64 * WAVES) void k_fwd_sweep(SweepArgs a, int nblk) {
+template <typename T, int Q, int MODE, int ET, bool HASG>
+__global__ __launch_bounds__(64 * WAVES) LP_NARROW_WAVES(Q) void k_fwd_sweep(SweepArgs a, int nblk) {
   constexpr int VQ = Q / 4;
   __shared__ double red[WAVES];
   const int lane = threadIdx.x & 63;
@@ -227,13 +233,13 @@ __global__ __launch_bounds__(64 * WAVES) void k_fwd_sweep(SweepArgs a, int nblk)
     const size_t n = (size_t)(kc + j) * a.stride;
     ld_fwd<T, Q>(s.w, K + n * (Q * Q), lane);
     ldv<T, VQ>(s.b, bb + n * Q);
-    if (G) {
+    if (HASG) {
 #pragma unroll
       for (int t = 0; t < ET; ++t) ldv<T, VQ>(s.g[t], G + (kc + j + 1) * slice + ex[t].row);
     }
   };
-  S cur;
-  if (nsteps > 0) fetch(cur, 0);
+  S s0, s1;
+  if (nsteps > 0) fetch(s0, 0);
   T v[ET][VQ], coarse[ET][VQ];
 #pragma unroll
   for (int t = 0; t < ET; ++t) {
@@ -249,24 +255,30 @@ __global__ __launch_bounds__(64 * WAVES) void k_fwd_sweep(SweepArgs a, int nblk)
       if (k > 0 && ex[t].on) stv<T, VQ>(X + kc * slice + ex[t].row, v[t]);
     }
   }
-  for (int j = 0; j < nsteps; ++j) {
-    S nxt;
-    fetch(nxt, j + 1 < nsteps ? j + 1 : j);
+  auto step = [&](const S& cur, int j) {
+    T s[ET * VQ];
+#pragma unroll
+    for (int t = 0; t < ET; ++t) prod<T, Q>(s + t * VQ, cur.w, v[t], cur.b);
+    apply<T, ET * VQ, false>(s, a.act);
 #pragma unroll
     for (int t = 0; t < ET; ++t) {
-      T s[VQ];
-      prod<T, Q>(s, cur.w, v[t], cur.b);
-      apply<T, VQ, false>(s, a.act);
 #pragma unroll
       for (int i = 0; i < VQ; ++i) {
         // coarse step Phi_{l+1} from the same C-point with the same weights
-        if (MODE == SWEEP_FRES && j == 0) coarse[t][i] = v[t][i] + hc * s[i];
-        v[t][i] = v[t][i] + hl * s[i];
-        if (G) v[t][i] += cur.g[t][i];
+        if (MODE == SWEEP_FRES && j == 0) coarse[t][i] = v[t][i] + hc * s[t * VQ + i];
+        v[t][i] = v[t][i] + hl * s[t * VQ + i];
+        if (HASG) v[t][i] += cur.g[t][i];
       }
       if (MODE == SWEEP_CORRF && ex[t].on) stv<T, VQ>(X + (kc + j + 1) * slice + ex[t].row, v[t]);
     }
-    cur = nxt;
+  };
+  // two steps at a time, so that the operands in flight change names and not registers
+  for (int j = 0; j < nsteps; j += 2) {
+    fetch(s1, min(j + 1, nsteps - 1));
+    step(s0, j);
+    if (j + 1 >= nsteps) break;
+    fetch(s0, min(j + 2, nsteps - 1));
+    step(s1, j + 1);
   }
 
   if (MODE == SWEEP_FC) {
@@ -309,8 +321,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_fwd_sweep(SweepArgs a, int nblk)
 }
 
 // sigma' of the step's layer, then w = K^T (sigma' * v)
-template <typename T, int Q, int MODE, int ET>
-__global__ __launch_bounds__(64 * WAVES) void k_adj_sweep(SweepArgs a, int nblk) {
+template <typename T, int Q, int MODE, int ET, bool HASG>
+__global__ __launch_bounds__(64 * WAVES) LP_NARROW_WAVES(Q) void k_adj_sweep(SweepArgs a, int nblk) {
   constexpr int VQ = Q / 4;
   __shared__ double red[WAVES];
   const int lane = threadIdx.x & 63;
@@ -339,11 +351,11 @@ __global__ __launch_bounds__(64 * WAVES) void k_adj_sweep(SweepArgs a, int nblk)
 #pragma unroll
     for (int t = 0; t < ET; ++t) {
       ldv<T, VQ>(s.u[t], Uf + n * slice + ex[t].row);
-      if (G) ldv<T, VQ>(s.g[t], G + (size_t)i * slice + ex[t].row);
+      if (HASG) ldv<T, VQ>(s.g[t], G + (size_t)i * slice + ex[t].row);
     }
   };
-  S cur;
-  if (nsteps > 0) fetch(cur, 0);
+  S s0, s1;
+  if (nsteps > 0) fetch(s0, 0);
   T v[ET][VQ], coarse[ET][VQ];  // FRES: coarse holds C_{k+1} until the last step, then the coarse step
 #pragma unroll
   for (int t = 0; t < ET; ++t) {
@@ -363,40 +375,47 @@ __global__ __launch_bounds__(64 * WAVES) void k_adj_sweep(SweepArgs a, int nblk)
       if (k + 1 < Nc && ex[t].on) stv<T, VQ>(X + top * slice + ex[t].row, v[t]);
     }
   }
-  for (int j = 0; j < nsteps; ++j) {
-    const long i = top - 1 - j;
-    // the transposed operand comes from the lines the forward one has brought in
-    Wt<T, Q> wt;
-    ld_tr<T, Q>(wt, K + (size_t)i * a.stride * (Q * Q), lane);
-    S nxt;
-    fetch(nxt, j + 1 < nsteps ? j + 1 : j);
+  T zero[VQ];
+#pragma unroll
+  for (int q = 0; q < VQ; ++q) zero[q] = T(0);
+  auto step = [&](const S& cur, const Wt<T, Q>& wt, int j) {
+    T d[ET * VQ];
+#pragma unroll
+    for (int t = 0; t < ET; ++t) prod<T, Q>(d + t * VQ, cur.w, cur.u[t], cur.b);
+    apply<T, ET * VQ, true>(d, a.act);
 #pragma unroll
     for (int t = 0; t < ET; ++t) {
-      T d[VQ], w[VQ], zero[VQ];
-#pragma unroll
-      for (int q = 0; q < VQ; ++q) zero[q] = T(0);
-      prod<T, Q>(d, cur.w, cur.u[t], cur.b);
-      apply<T, VQ, true>(d, a.act);
+      T w[VQ], x[VQ];
       if (MODE == SWEEP_FRES && j == c - 1) {
         // coarse adjoint step from the upper C-point, linearised at the same fine state
-        T s2[VQ];
 #pragma unroll
-        for (int q = 0; q < VQ; ++q) s2[q] = d[q] * coarse[t][q];
-        prod<T, Q>(w, wt, s2, zero);
+        for (int q = 0; q < VQ; ++q) x[q] = d[t * VQ + q] * coarse[t][q];
+        prod<T, Q>(w, wt, x, zero);
 #pragma unroll
         for (int q = 0; q < VQ; ++q) coarse[t][q] = coarse[t][q] + hc * w[q];
       }
 #pragma unroll
-      for (int q = 0; q < VQ; ++q) d[q] *= v[t][q];
-      prod<T, Q>(w, wt, d, zero);
+      for (int q = 0; q < VQ; ++q) x[q] = d[t * VQ + q] * v[t][q];
+      prod<T, Q>(w, wt, x, zero);
 #pragma unroll
       for (int q = 0; q < VQ; ++q) {
         v[t][q] = v[t][q] + hl * w[q];
-        if (G) v[t][q] += cur.g[t][q];
+        if (HASG) v[t][q] += cur.g[t][q];
       }
-      if (MODE == SWEEP_CORRF && ex[t].on) stv<T, VQ>(X + (size_t)i * slice + ex[t].row, v[t]);
+      if (MODE == SWEEP_CORRF && ex[t].on) stv<T, VQ>(X + (top - 1 - j) * slice + ex[t].row, v[t]);
     }
-    cur = nxt;
+  };
+  // two steps at a time, so that the operands in flight change names and not
+  // registers; the transposed operand comes from the lines the forward one brought in
+  for (int j = 0; j < nsteps; j += 2) {
+    Wt<T, Q> wt;
+    ld_tr<T, Q>(wt, K + (size_t)(top - 1 - j) * a.stride * (Q * Q), lane);
+    fetch(s1, min(j + 1, nsteps - 1));
+    step(s0, wt, j);
+    if (j + 1 >= nsteps) break;
+    ld_tr<T, Q>(wt, K + (size_t)(top - 2 - j) * a.stride * (Q * Q), lane);
+    fetch(s0, min(j + 2, nsteps - 1));
+    step(s1, wt, j + 1);
   }
 
   if (MODE == SWEEP_FC) {
@@ -443,7 +462,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_adj_sweep(SweepArgs a, int nblk)
 // be in flight early, so D steps of them are kept in a register ring (indices
 // clamped to valid layers and rows, so that every load is issued unconditionally).
 template <typename T, int Q>
-__global__ __launch_bounds__(64) void k_fwd_serial(SerialArgs a) {
+__global__ __launch_bounds__(64) LP_NARROW_WAVES(Q) void k_fwd_serial(SerialArgs a) {
   constexpr int VQ = Q / 4, D = Q <= 16 ? 4 : 2;
   const int lane = threadIdx.x & 63;
   const Ex ex = example<Q>(blockIdx.x, a.B);
@@ -486,7 +505,7 @@ __global__ __launch_bounds__(64) void k_fwd_serial(SerialArgs a) {
 }
 
 template <typename T, int Q>
-__global__ __launch_bounds__(64) void k_adj_serial(SerialArgs a) {
+__global__ __launch_bounds__(64) LP_NARROW_WAVES(Q) void k_adj_serial(SerialArgs a) {
   constexpr int VQ = Q / 4, D = Q <= 16 ? 4 : 2;
   const int lane = threadIdx.x & 63;
   const Ex ex = example<Q>(blockIdx.x, a.B);
@@ -541,7 +560,7 @@ __global__ __launch_bounds__(64) void k_adj_serial(SerialArgs a) {
 // Workgroup (n, y): forward r = Phi_n(U[n]) - U[n+1]; adjoint r = Phibar_n(Lam[n+1])
 // - Lam[n]; writes the block's sum of r^2.
 template <typename T, int Q, int DIR>
-__global__ __launch_bounds__(64 * WAVES) void k_resid(ResidArgs a, int nblk) {
+__global__ __launch_bounds__(64 * WAVES) LP_NARROW_WAVES(Q) void k_resid(ResidArgs a, int nblk) {
   constexpr int VQ = Q / 4;
   __shared__ double red[WAVES];
   const int lane = threadIdx.x & 63;
@@ -605,7 +624,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 template <typename T, int Q>
-__global__ __launch_bounds__(64 * WAVES) void k_grad(GradArgs a) {
+__global__ __launch_bounds__(64 * WAVES) LP_NARROW_WAVES(Q) void k_grad(GradArgs a) {
   using D = Dim<Q>;
   constexpr int VQ = D::VQ, NB = D::NB, LD = Q + 16 / (int)sizeof(T);
   constexpr int NOUT = Q * Q + Q;
@@ -746,7 +765,7 @@ __global__ __launch_bounds__(256) void k_grad_final(GradArgs a, int nw, int nbia
 
 // ------------------------------------------------------------------ launchers
 
-template <typename T, int Q, int ET>
+template <typename T, int Q, int ET, bool HASG>
 hipError_t sweep_et(int dir, const SweepArgs& a, hipStream_t st, int* partials) {
   const long nblk = (a.B + 16L * WAVES * ET - 1) / (16L * WAVES * ET), grid = (a.Nl / a.c) * nblk;
   if (grid > 0x7fffffffL) return hipErrorNotSupported;
@@ -754,13 +773,13 @@ hipError_t sweep_et(int dir, const SweepArgs& a, hipStream_t st, int* partials) 
   const dim3 gd((unsigned)grid);
   const int nb = (int)nblk;
   if (dir == DIR_FWD) {
-    if (a.mode == SWEEP_FC) launch(k_fwd_sweep<T, Q, SWEEP_FC, ET>, gd, 64 * WAVES, 0, st, a, nb);
-    else if (a.mode == SWEEP_FRES) launch(k_fwd_sweep<T, Q, SWEEP_FRES, ET>, gd, 64 * WAVES, 0, st, a, nb);
-    else launch(k_fwd_sweep<T, Q, SWEEP_CORRF, ET>, gd, 64 * WAVES, 0, st, a, nb);
+    if (a.mode == SWEEP_FC) launch(k_fwd_sweep<T, Q, SWEEP_FC, ET, HASG>, gd, 64 * WAVES, 0, st, a, nb);
+    else if (a.mode == SWEEP_FRES) launch(k_fwd_sweep<T, Q, SWEEP_FRES, ET, HASG>, gd, 64 * WAVES, 0, st, a, nb);
+    else launch(k_fwd_sweep<T, Q, SWEEP_CORRF, ET, HASG>, gd, 64 * WAVES, 0, st, a, nb);
   } else {
-    if (a.mode == SWEEP_FC) launch(k_adj_sweep<T, Q, SWEEP_FC, ET>, gd, 64 * WAVES, 0, st, a, nb);
-    else if (a.mode == SWEEP_FRES) launch(k_adj_sweep<T, Q, SWEEP_FRES, ET>, gd, 64 * WAVES, 0, st, a, nb);
-    else launch(k_adj_sweep<T, Q, SWEEP_CORRF, ET>, gd, 64 * WAVES, 0, st, a, nb);
+    if (a.mode == SWEEP_FC) launch(k_adj_sweep<T, Q, SWEEP_FC, ET, HASG>, gd, 64 * WAVES, 0, st, a, nb);
+    else if (a.mode == SWEEP_FRES) launch(k_adj_sweep<T, Q, SWEEP_FRES, ET, HASG>, gd, 64 * WAVES, 0, st, a, nb);
+    else launch(k_adj_sweep<T, Q, SWEEP_CORRF, ET, HASG>, gd, 64 * WAVES, 0, st, a, nb);
   }
   return hipGetLastError();
 }
@@ -771,9 +790,10 @@ hipError_t sweep_et(int dir, const SweepArgs& a, hipStream_t st, int* partials) 
 template <typename T, int Q>
 hipError_t sweep(int dir, const SweepArgs& a, hipStream_t st, int* partials) {
   if constexpr (Q <= 16) {
-    if ((long)(a.Nl / a.c) * ((a.B + 31) / 32) >= 8192) return sweep_et<T, Q, 2>(dir, a, st, partials);
+    if ((long)(a.Nl / a.c) * ((a.B + 31) / 32) >= 8192)
+      return a.G ? sweep_et<T, Q, 2, true>(dir, a, st, partials) : sweep_et<T, Q, 2, false>(dir, a, st, partials);
   }
-  return sweep_et<T, Q, 1>(dir, a, st, partials);
+  return a.G ? sweep_et<T, Q, 1, true>(dir, a, st, partials) : sweep_et<T, Q, 1, false>(dir, a, st, partials);
 }
 
 template <typename T, int Q>

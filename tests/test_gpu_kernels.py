@@ -12,7 +12,7 @@ import torch
 from paper_1812_04352_amd import lp as L
 
 pytestmark = pytest.mark.gpu
-U = {"f32": 2.0 ** -24, "f64": 2.0 ** -53}
+EPS = {"f32": 2.0 ** -24, "f64": 2.0 ** -53}
 DT = {"f32": torch.float32, "f64": torch.float64}
 
 
@@ -65,13 +65,13 @@ def test_dense_opening(dtype, act_name, B, q, nf):
     L.lp_open_grad(p, L.LP_OPEN_DENSE_ACT, nf, y, Lw, lam, dL)
     y, Lw, lam = y.double(), Lw.double(), lam.double()
     z, za = y @ Lw.T.contiguous(), y.abs() @ Lw.abs().T.contiguous()
-    within(u0, act(z, act_name), za + 0.025, 4 * (nf + 8) * U[dtype], "u0")
+    within(u0, act(z, act_name), za + 0.025, 4 * (nf + 8) * EPS[dtype], "u0")
     s = dact(z, act_name) * lam
     # sigma' changes by at most 5 |dz|; a ReLU site within rounding of zero may go either way
     scale = (lam.abs() * (1.0 + 5.0 * za)).T.contiguous() @ y.abs()
-    bound = 4 * (nf + B + 8) * U[dtype]
+    bound = 4 * (nf + B + 8) * EPS[dtype]
     if act_name == "relu":
-        open_sites = (z.abs() <= 4 * (nf + 8) * U[dtype] * za).double() * lam.abs()
+        open_sites = (z.abs() <= 4 * (nf + 8) * EPS[dtype] * za).double() * lam.abs()
         scale = scale + (open_sites.T.contiguous() @ y.abs()) / bound
     within(dL, s.T.contiguous() @ y, scale, bound, "dL")
 
@@ -91,7 +91,7 @@ def test_conv_opening_gradient(act_name, B, H, W):
     s = dact(z, act_name) * lam
     ref = torch.stack([(s * t[:, None]).sum((0, 2, 3)) for t in taps], 1)
     scale = torch.stack([(lam.abs() * (1.0 + 5.0 * za) * t.abs()[:, None]).sum((0, 2, 3)) for t in taps], 1)
-    within(dL.reshape(8, 9), ref, scale, 4 * (9 + 8 + 32) * U["f32"], "dL")
+    within(dL.reshape(8, 9), ref, scale, 4 * (9 + 8 + 32) * EPS["f32"], "dL")
 
 
 # staged in LDS up to 64 KB, one workgroup (or wave) per example beyond
@@ -114,5 +114,86 @@ def test_head_and_accuracy(layer, B, C, H, W, nc):
     torch.testing.assert_close(J[0], -(c * torch.log_softmax(z, 1)).sum() / B, rtol=1e-12, atol=1e-12)
     for got, ref, s in ((lam, d @ Wc, d.abs() @ Wc.abs()), (dW, d.T.contiguous() @ u, d.abs().T.contiguous() @ u.abs()),
                         (dmu, d.sum(0), d.abs().sum(0))):
-        within(got, ref, s, 2 * U["f32"], "head")  # summed in fp64, rounded once
+        within(got, ref, s, 2 * EPS["f32"], "head")  # summed in fp64, rounded once
     assert float(acc) == float((z.argmax(1) == c.argmax(1)).double().mean())
+
+
+NARROW = [("f64", 8), ("f64", 16), ("f64", 32), ("f32", 8), ("f32", 16)]
+
+
+def dense_problem(dtype, q, act_name, N, B, seed=0, h=0.05):
+    p = L.problem(dtype, "dense", act_name, N, B, q, h=h)
+    # weights at an odd offset of a flat vector: element alignment is all that is promised
+    flat = rnd(seed + 1, 1 + N * q * q, dtype=DT[dtype], std=0.5 * q ** -0.5)
+    K, b = flat[1:].view(N, q, q), rnd(seed + 2, 1 + N * q, dtype=DT[dtype], std=0.1)[1:].view(N, q)
+    U = torch.full((N + 1, B, q), float("nan"), device="cuda", dtype=DT[dtype])
+    Lam = torch.full_like(U, float("nan"))
+    U[0], Lam[N] = rnd(seed + 3, B, q, dtype=DT[dtype]), rnd(seed + 4, B, q, dtype=DT[dtype])
+    return p, K, b, U, Lam
+
+
+def serial_reference(K, b, U, Lam, a, h):
+    """Trajectory, adjoint, gradient and residual norms in 64 bits, layer by layer."""
+    K, b, N = K.double(), b.double(), K.shape[0]
+    u = [U[0].double()]
+    for n in range(N):
+        u.append(u[-1] + h * act(u[-1] @ K[n].T.contiguous() + b[n], a))
+    lam, dK, db = [Lam[N].double()], [], []
+    for n in reversed(range(N)):
+        s = dact(u[n] @ K[n].T.contiguous() + b[n], a) * lam[0]
+        dK.insert(0, h * (s.T.contiguous() @ u[n]))
+        db.insert(0, h * s.sum(0))
+        lam.insert(0, lam[0] + h * (s @ K[n]))
+    return torch.stack(u), torch.stack(lam), torch.stack(dK), torch.stack(db)
+
+
+# tiles of 16 examples per wave, 64 per sweep workgroup; smooth activations (no sites
+# that rounding decides). The error of N = 6 layers grows by at most (1 + 5 h |K|)^2
+# per layer, far below 16 here, so 16 (N (q + 8)) u bounds it; the gradient adds B terms.
+@pytest.mark.parametrize("B", [1, 15, 17, 64, 129])
+@pytest.mark.parametrize("dtype,q", NARROW)
+def test_narrow_dense_layers(dtype, q, B):
+    for a in ("tanh", "smoothrelu", "identity"):
+        N, h = 6, 0.05
+        p, K, b, U, Lam = dense_problem(dtype, q, a, N, B)
+        dK, db, ws = torch.empty_like(K), torch.empty_like(b), L.alloc_workspace(p)
+        L.lp_serial_forward(p, K, b, U)
+        L.lp_serial_adjoint(p, K, b, U, Lam)
+        L.lp_gradient(p, K, b, U, Lam, dK, db, ws)
+        ref = serial_reference(K, b, U, Lam, a, h)
+        bound = 16 * N * (q + 8) * EPS[dtype]
+        for got, r, n in ((U, ref[0], 0), (Lam, ref[1], 0), (dK, ref[2], B), (db, ref[3], B)):
+            e = float((got.double() - r).norm() / r.norm())
+            assert e <= bound + 4 * n * EPS[dtype], (a, e, bound)
+        # residuals of a perturbed pair against the definition
+        V, M = U + 1e-3 * rnd(7, *U.shape, dtype=DT[dtype]), Lam + 1e-3 * rnd(8, *U.shape, dtype=DT[dtype])
+        z = torch.bmm(V[:-1].double(), K.double().transpose(1, 2).contiguous()) + b.double()[:, None]
+        rs = V[:-1].double() + h * act(z, a) - V[1:].double()
+        ra = M[1:].double() + h * torch.bmm(dact(z, a) * M[1:].double(), K.double().contiguous()) - M[:-1].double()
+        for which, r in ((L.LP_STATE, rs), (L.LP_ADJOINT, ra)):
+            got = L.lp_residual_norm(p, which, K, b, V, M, ws)
+            assert abs(got - float(r.norm())) <= bound * float(V.double().norm() + M.double().norm())
+
+
+# two tiles per wave from 8192 pairs of tiles per sweep on (256 intervals x 32 here):
+# examples are independent, so a part of the batch solved alone gives the same bits
+@pytest.mark.parametrize("dtype,q", NARROW)
+def test_narrow_two_tiles_per_wave(dtype, q):
+    N, B = 1024, 1037
+    p, K, b, U, Lam = dense_problem(dtype, q, "tanh", N, B, h=0.005)
+    mg = L.mgrit(cf=4, max_levels=3, max_iter=2)
+
+    def solve(U0, LN):
+        ps = L.problem(dtype, "dense", "tanh", N, U0.shape[0], q, h=0.005)
+        u, lam = (torch.full((N + 1,) + U0.shape, float("nan"), device="cuda", dtype=DT[dtype]) for _ in range(2))
+        u[0], lam[N] = U0, LN
+        ws = L.alloc_workspace(ps, mg)
+        L.lp_mgrit_forward(ps, mg, K, b, u, ws)
+        L.lp_mgrit_adjoint(ps, mg, K, b, u, lam, ws)
+        return u, lam
+
+    u, lam = solve(U[0], Lam[N])
+    assert bool(torch.isfinite(u).all()) and bool(torch.isfinite(lam).all())
+    for part in (slice(0, 33), slice(1000, 1037)):
+        us, ls = solve(U[0][part].contiguous(), Lam[N][part].contiguous())
+        assert torch.equal(us, u[:, part]) and torch.equal(ls, lam[:, part])
