@@ -3,27 +3,35 @@
 //
 // At this width a layer step is a real dense contraction (2 q^2 = 96.8 kflop per
 // example against 2 q e = 1.8 kB of state traffic), so the kernels are bound by
-// the matrix cores, not by HBM. One layer's weights (q^2 fp32 = 194 kB) no longer
-// fit in LDS next to anything else, so every product streams K_n through LDS in
-// panels of 32 contraction indices, double-buffered: the next panel is fetched
-// into registers while the current one feeds the matrix cores, then written to
-// the other buffer behind one barrier.
+// the matrix cores, not by HBM, and run their products as split bf16 ones
+// (lp_split.h).
 //
-// Layout (v_mfma_f32_16x16x4_f32, 16 examples per wave, 4 waves per workgroup):
-// the width is padded to QP = 224 = 14 blocks of 16 features; register r of
-// block mb in lane l holds feature 16 mb + 4 (l/16) + r of example l%16. That
-// accumulator layout is the B operand of the next product when the A operand
-// supplies, for k-slice (ib, r), the contraction index 16 ib + 4 (l/16) + r, so
-// chained steps keep the state in the lanes that own it. Padding features
-// (220..223) are never loaded or stored; the padded rows and columns of the LDS
-// panels are zero and the padded values of every new state are reset to zero
-// after the activation (sigma(0) is not zero for the smoothed ReLU).
+// A workgroup runs T tiles of 16 examples on NP = 7 waves; the width is padded to
+// QP = 224 = 7 panels of 32 features and wave w owns the features of panel w: their
+// rows of K_n (or of K_n^T) are the wave's alone, so the weights go from L2 straight
+// to its registers, and their state values of all T tiles lie in its registers in
+// accumulator layout: register r of block m (0, 1) of tile t in lane l holds feature
+// 32 w + 16 m + 4 (l/16) + r of example l%16. What the other waves need of it is the
+// B operand, and that is the same layout again: for contraction panel p the eight
+// values of a lane are blocks 0 and 1 of wave p. So after each step a wave splits
+// its new values and writes them to LDS as fragments [tile][panel][part][lane] of 16
+// bytes, one conflict-free write and, for the readers, one conflict-free read per
+// lane, with a barrier before and after. A fragment read feeds 12 matrix
+// instructions, a weight fragment 6 T; the waves run a whole layer between barriers.
+// Padding features (220..223) are never loaded or stored, their weights are zero,
+// and the padded values of every new state are reset to zero after the activation
+// (sigma(0) is not zero for the smoothed ReLU).
 //
-//   forward product  z = K_n v + b_n : panel p holds K_n[:, 32p .. 32p+31] as
-//                    [output][32] rows (pitch 36: a 16-byte read per lane, the
-//                    16 lanes of a group on disjoint banks);
-//   adjoint product  w = K_n^T s     : panel p holds K_n[32p .. 32p+31, :] as
-//                    [32][output] rows (pitch 228: four lane groups 16 banks apart).
+// T = 6 takes 126 kB of LDS, one workgroup per CU, two waves per SIMD on three SIMDs
+// and one on the fourth; sweeps with fewer workgroups than CUs take T = 4 or 2.
+// Streaming K_n through LDS instead, in panels that all waves read for their own 16
+// examples, needs a barrier per panel and as much LDS time as matrix time. Finest
+// sweeps of 1000 examples and 1024 layers, us: forward FC 1106 (panels, fp32
+// instructions), 840 (panels, split products), 725 (this form); forward FRES 1133,
+// 890, 780; adjoint FC 1097, 835, 815; adjoint FRES 1433, 1480, 1020. The matrix
+// pipes are busy 39 % of the time: a layer's activations, splits and barriers come at
+// the same time for all waves, and one workgroup fills the CU. (Reading fragments and
+// splitting weights a pair of tiles ahead was not faster: its registers spill.)
 //
 // Sweep modes, the record of sigma' and the FAS bookkeeping follow Algorithm 1
 // (Section 3.1) exactly as the other dense kernels do.
@@ -32,6 +40,7 @@
 
 #include "lp_device.h"
 #include "lp_internal.h"
+#include "lp_split.h"
 
 namespace lp {
 namespace wide {
@@ -40,139 +49,146 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int MODE_SERIAL = 3;
-constexpr int WAVES = 4;
-constexpr int NT = 64 * WAVES;
-constexpr int EX = 16;  // examples per wave
 
 template <int Q>
 struct Geo {
   static_assert(Q % 4 == 0, "rows are read as 16-byte vectors");
   static constexpr int QP = (Q + 31) / 32 * 32;  // padded width
-  static constexpr int NB = QP / 16;             // 16-feature blocks (even: QP is a multiple of 32)
-  static constexpr int NP = QP / 32;             // panels per layer
-  static constexpr int PLF = 32 + 4;             // forward panel pitch (floats)
-  static constexpr int PLA = QP + 4;             // adjoint panel pitch (floats)
-  static constexpr int PSZ = QP * PLF > 32 * PLA ? QP * PLF : 32 * PLA;
-  static constexpr int PV = QP * 32 / 4;         // 16-byte slots of a panel
-  static constexpr int PPT = (PV + NT - 1) / NT;
-  // block NB-1 is real for lane groups g < TG (the rest is padding)
-  static constexpr int TG = (Q - 16 * (NB - 1)) / 4;
+  static constexpr int NP = QP / 32;             // panels, waves per workgroup
+  static constexpr int NT = 64 * NP;
+  static constexpr int NF = 3 * 64 * NP;         // fragments per tile
+};
+
+// The lane's place: its panel (wave), lane group and example, and whether its second
+// block is real (the first always is: only the last panel is cut short).
+template <int Q, int T>
+struct Ctx {
+  int lane, g, w;
+  bool ok1;
+  size_t row[T];  // element offset of (example of tile t, feature 32 w + 4 g) in a state row block
+  bool on[T];
+  __device__ Ctx(int tile, int B) {
+    lane = threadIdx.x & 63;
+    g = lane >> 4;
+    w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    ok1 = 32 * w + 16 + 4 * g < Q;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int e = (tile * T + t) * 16 + (lane & 15);
+      on[t] = e < B;
+      row[t] = (size_t)(on[t] ? e : 0) * Q + 32 * w + 4 * g;
+    }
+  }
 };
 
 // ------------------------------------------------------------------ rows
-// p points at the example's row + 4 g (g = lane / 16)
-template <int Q>
-__device__ __forceinline__ void load_row(f32x4 (&v)[Geo<Q>::NB], const float* __restrict__ p, int g) {
-  constexpr int NB = Geo<Q>::NB;
-#pragma unroll
-  for (int mb = 0; mb < NB; ++mb)
-    v[mb] = (mb < NB - 1 || g < Geo<Q>::TG) ? *reinterpret_cast<const f32x4*>(p + 16 * mb) : f32x4{};
+template <int T>
+using Val = f32x4[T][2];  // a wave's values of its T tiles
+
+// one tile's two blocks at p (the lane's element of the example's row)
+__device__ __forceinline__ void load2(f32x4 (&v)[2], const float* __restrict__ p, bool ok1) {
+  v[0] = *reinterpret_cast<const f32x4*>(p);
+  v[1] = ok1 ? *reinterpret_cast<const f32x4*>(p + 16) : f32x4{};
+}
+__device__ __forceinline__ void store2(float* __restrict__ p, const f32x4 (&v)[2], bool ok1) {
+  *reinterpret_cast<f32x4*>(p) = v[0];
+  if (ok1) *reinterpret_cast<f32x4*>(p + 16) = v[1];
 }
 
-template <int Q>
-__device__ __forceinline__ void store_row(float* __restrict__ p, const f32x4 (&v)[Geo<Q>::NB], int g) {
-  constexpr int NB = Geo<Q>::NB;
+// all tiles, from the row block at base; lanes past the batch read example 0's row
+// (valid memory; every example is its own column of the products) and store nothing
+template <int Q, int T>
+__device__ __forceinline__ void load_rows(Val<T>& v, const float* __restrict__ base, const Ctx<Q, T>& c) {
 #pragma unroll
-  for (int mb = 0; mb < NB; ++mb)
-    if (mb < NB - 1 || g < Geo<Q>::TG) *reinterpret_cast<f32x4*>(p + 16 * mb) = v[mb];
+  for (int t = 0; t < T; ++t) load2(v[t], base + c.row[t], c.ok1);
+}
+template <int Q, int T>
+__device__ __forceinline__ void store_rows(float* __restrict__ base, const Val<T>& v, const Ctx<Q, T>& c) {
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+    if (c.on[t]) store2(base + c.row[t], v[t], c.ok1);
 }
 
-// The sigma' record at element offset off: one byte (0/1) per value for ReLU,
-// fp32 otherwise.
-template <int Q>
-__device__ __forceinline__ void load_dsig(f32x4 (&d)[Geo<Q>::NB], const void* rec, size_t off, int act, int g) {
-  constexpr int NB = Geo<Q>::NB;
+// The sigma' record at element offset off: one byte (0/1) per value for ReLU, fp32
+// otherwise.
+__device__ __forceinline__ void load_dsig(f32x4 (&d)[2], const void* rec, size_t off, int act, bool ok1) {
   if (act == ACT_RELU) {
     const uint8_t* p = static_cast<const uint8_t*>(rec) + off;
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) {
-      const uint32_t w = (mb < NB - 1 || g < Geo<Q>::TG) ? *reinterpret_cast<const uint32_t*>(p + 16 * mb) : 0u;
+    for (int m = 0; m < 2; ++m) {
+      const uint32_t x = m == 0 || ok1 ? *reinterpret_cast<const uint32_t*>(p + 16 * m) : 0u;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) d[mb][r] = (w >> (8 * r)) & 0xffu ? 1.f : 0.f;
+      for (int r = 0; r < 4; ++r) d[m][r] = (x >> (8 * r)) & 0xffu ? 1.f : 0.f;
     }
   } else {
-    load_row<Q>(d, static_cast<const float*>(rec) + off, g);
+    load2(d, static_cast<const float*>(rec) + off, ok1);
   }
 }
-
-template <int Q>
-__device__ __forceinline__ void store_dsig(void* rec, size_t off, int act, const f32x4 (&d)[Geo<Q>::NB], int g) {
-  constexpr int NB = Geo<Q>::NB;
+__device__ __forceinline__ void store_dsig(void* rec, size_t off, int act, const f32x4 (&d)[2], bool ok1) {
   if (act == ACT_RELU) {
     uint8_t* p = static_cast<uint8_t*>(rec) + off;
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) {
-      uint32_t w = 0;
+    for (int m = 0; m < 2; ++m) {
+      uint32_t x = 0;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) w |= (d[mb][r] != 0.f ? 1u : 0u) << (8 * r);
-      if (mb < NB - 1 || g < Geo<Q>::TG) *reinterpret_cast<uint32_t*>(p + 16 * mb) = w;
+      for (int r = 0; r < 4; ++r) x |= (d[m][r] != 0.f ? 1u : 0u) << (8 * r);
+      if (m == 0 || ok1) *reinterpret_cast<uint32_t*>(p + 16 * m) = x;
     }
   } else {
-    store_row<Q>(static_cast<float*>(rec) + off, d, g);
+    store2(static_cast<float*>(rec) + off, d, ok1);
   }
 }
 
-// sigma (deriv = false) or sigma' (deriv = true) of every value; padding values
-// are reset to zero
-template <int Q>
-__device__ __forceinline__ void apply(f32x4 (&z)[Geo<Q>::NB], int act, bool deriv, int g) {
-  constexpr int NB = Geo<Q>::NB;
+// sigma (deriv = false) or sigma' (deriv = true) of every value; padding values are
+// reset to zero
+template <int ACT, bool DERIV, int T>
+__device__ __forceinline__ void apply_one(Val<T>& z) {
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z[t][m][r] = DERIV ? dact_f<float, ACT>(z[t][m][r]) : act_f<float, ACT>(z[t][m][r]);
+}
+template <bool DERIV, int T>
+__device__ __forceinline__ void apply(Val<T>& z, int act, bool ok1) {
   switch (act) {
-    case ACT_TANH:
-#pragma unroll
-      for (int mb = 0; mb < NB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          z[mb][r] = deriv ? dact_f<float, ACT_TANH>(z[mb][r]) : act_f<float, ACT_TANH>(z[mb][r]);
-      break;
-    case ACT_RELU:
-#pragma unroll
-      for (int mb = 0; mb < NB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          z[mb][r] = deriv ? (z[mb][r] > 0.f ? 1.f : 0.f) : (z[mb][r] > 0.f ? z[mb][r] : 0.f);
-      break;
-    case ACT_SMOOTHRELU:
-#pragma unroll
-      for (int mb = 0; mb < NB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          z[mb][r] = deriv ? dact_f<float, ACT_SMOOTHRELU>(z[mb][r]) : act_f<float, ACT_SMOOTHRELU>(z[mb][r]);
-      break;
-    default:
-      if (deriv) {
-#pragma unroll
-        for (int mb = 0; mb < NB; ++mb) z[mb] = 1.f;
-      }
-      break;
+    case ACT_TANH: apply_one<ACT_TANH, DERIV, T>(z); break;
+    case ACT_RELU: apply_one<ACT_RELU, DERIV, T>(z); break;
+    case ACT_SMOOTHRELU: apply_one<ACT_SMOOTHRELU, DERIV, T>(z); break;
+    default: if (DERIV) apply_one<ACT_IDENTITY, DERIV, T>(z); break;
   }
-  if (g >= Geo<Q>::TG) z[NB - 1] = 0.f;
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+    if (!ok1) z[t][1] = 0.f;
 }
 
 // v = c + (v' - c) (Algorithm 1, the coarse-grid correction of a C-point)
-template <int Q>
-__device__ __forceinline__ void correct(f32x4 (&v)[Geo<Q>::NB], const float* cs, const float* vs, int g) {
-  constexpr int NB = Geo<Q>::NB;
-  f32x4 cv[NB], vv[NB];
-  load_row<Q>(cv, cs, g);
-  load_row<Q>(vv, vs, g);
+template <int Q, int T>
+__device__ __forceinline__ void correct(Val<T>& v, const float* cs, const float* vs, const Ctx<Q, T>& c) {
 #pragma unroll
-  for (int mb = 0; mb < NB; ++mb) v[mb] = cv[mb] + (vv[mb] - cv[mb]);
+  for (int t = 0; t < T; ++t) {
+    f32x4 a[2], b[2];
+    load2(a, cs + c.row[t], c.ok1);
+    load2(b, vs + c.row[t], c.ok1);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) v[t][m] = a[m] + (b[m] - a[m]);
+  }
 }
 
-template <int Q>
-__device__ __forceinline__ double sq_diff(const f32x4 (&a)[Geo<Q>::NB], const f32x4 (&b)[Geo<Q>::NB]) {
+__device__ __forceinline__ double sq_diff(const f32x4 (&a)[2], const f32x4 (&b)[2]) {
   double acc = 0.0;
 #pragma unroll
-  for (int mb = 0; mb < Geo<Q>::NB; ++mb)
+  for (int m = 0; m < 2; ++m)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float d = a[mb][r] - b[mb][r];
+      const float d = a[m][r] - b[m][r];
       acc += (double)d * (double)d;
     }
   return acc;
 }
 
+template <int W>
 __device__ __forceinline__ double wg_sum(double v, double* red) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -180,179 +196,78 @@ __device__ __forceinline__ double wg_sum(double v, double* red) {
   __syncthreads();
   double s = 0.0;
   if (threadIdx.x == 0)
-    for (int w = 0; w < WAVES; ++w) s += red[w];
+    for (int w = 0; w < W; ++w) s += red[w];
   return s;
 }
 
-// ------------------------------------------------------------------ panels
-// One panel in flight between global memory and LDS (PPT 16-byte slots per thread).
-template <int Q>
-struct Pan {
-  f32x4 r[Geo<Q>::PPT];
+// ------------------------------------------------------------------ products
+// The wave's weights of one contraction panel on their way to its registers: A
+// operand rows 32 w + 16 m + lane % 16, contraction 32 p + 16 h + 4 g + (0..3), of
+// K_n (TR false) or of K_n^T. Addresses are a uniform base and 32-bit lane offsets.
+// Past the width a valid weight of the same row (or, for a padded row, of row 0) is
+// read instead: padded state values are zero, and padded results are discarded.
+struct Raw {
+  f32x4 r[2][2];
 };
-
-// forward panel p of K_n: slot = (output row o, 4 columns c4) of K_n[:, 32p + 4 c4 ..]
-template <int Q>
-__device__ __forceinline__ void fetch_f(Pan<Q>& pr, const float* __restrict__ Kn, int p) {
-  using G = Geo<Q>;
-  const float* base = Kn + 32 * p;  // workgroup-uniform; 32-bit per-slot offsets
+template <int Q, bool TR>
+__device__ __forceinline__ void fetch_a(Raw& a, const float* __restrict__ Kn, int p, int w, int lane) {
+  const int i = lane & 15, k0 = 4 * (lane >> 4);
+  const char* base = reinterpret_cast<const char*>(Kn + (TR ? 32 * p * Q : 32 * p));
 #pragma unroll
-  for (int s = 0; s < G::PPT; ++s) {
-    const int idx = threadIdx.x + s * NT;
-    const int o = idx >> 3, c4 = idx & 7;
-    const bool ok = idx < G::PV && o < Q && 32 * p + 4 * c4 < Q;
-    pr.r[s] = ok ? *reinterpret_cast<const f32x4*>(base + (o * Q + 4 * c4)) : f32x4{};
-  }
-}
-
-template <int Q>
-__device__ __forceinline__ void put_f(float* buf, const Pan<Q>& pr) {
-  using G = Geo<Q>;
-#pragma unroll
-  for (int s = 0; s < G::PPT; ++s) {
-    const int idx = threadIdx.x + s * NT;
-    if (idx < G::PV) *reinterpret_cast<f32x4*>(buf + (idx >> 3) * G::PLF + 4 * (idx & 7)) = pr.r[s];
-  }
-}
-
-// adjoint panel p of K_n: slot = (row ii, 4 columns o4) of K_n[32p + ii][4 o4 ..];
-// slots S0 .. S1-1 of this thread (the adjoint moves a panel in two parts)
-template <int Q, int S0, int S1>
-__device__ __forceinline__ void fetch_a(f32x4 (&r)[S1 - S0], const float* __restrict__ Kn, int p) {
-  using G = Geo<Q>;
-  constexpr int RW = G::QP / 4;  // slots per panel row
-  // a workgroup-uniform panel base and 32-bit per-slot offsets (few registers)
-  const float* base = Kn + (size_t)(32 * p) * Q;
-#pragma unroll
-  for (int s = S0; s < S1; ++s) {
-    const int idx = threadIdx.x + s * NT;
-    const int ii = idx / RW, o4 = idx - ii * RW;
-    const bool ok = idx < G::PV && 32 * p + ii < Q && 4 * o4 < Q;
-    r[s - S0] = ok ? *reinterpret_cast<const f32x4*>(base + (ii * Q + 4 * o4)) : f32x4{};
-  }
-}
-
-template <int Q, int S0, int S1>
-__device__ __forceinline__ void put_a(float* buf, const f32x4 (&r)[S1 - S0]) {
-  using G = Geo<Q>;
-  constexpr int RW = G::QP / 4;
-#pragma unroll
-  for (int s = S0; s < S1; ++s) {
-    const int idx = threadIdx.x + s * NT;
-    const int ii = idx / RW, o4 = idx - ii * RW;
-    if (idx < G::PV) *reinterpret_cast<f32x4*>(buf + ii * G::PLA + 4 * o4) = r[s - S0];
-  }
-}
-
-// Consecutive forward products share the two panel buffers as a chain: a
-// product's last panel fetches the next product's first panel (the next layer is
-// known), so a step does not start with a panel load the whole workgroup waits
-// for. With an odd number of panels the buffer holding a product's first panel
-// alternates; `ph` tracks it and `ready` says whether it is already loaded. (The
-// transposed product does not chain: the extra state spilled in the adjoint
-// kernels and measured slower.)
-struct Chain {
-  int ph = 0;
-  bool ready = false;
-};
-
-// z = K_n v + b_n. Every thread of the workgroup calls it (it holds barriers).
-// Knext: the next product's weights (same kind), whose first panel this product
-// loads during its last one; nullptr ends the chain.
-template <int Q>
-__device__ __forceinline__ void prod(f32x4 (&z)[Geo<Q>::NB], const f32x4 (&v)[Geo<Q>::NB],
-                                     const float* __restrict__ Kn, const float* __restrict__ bn, float* buf,
-                                     int lane, Chain& ch, const float* __restrict__ Knext = nullptr) {
-  using G = Geo<Q>;
-  constexpr int NB = G::NB;
-  const int g = lane >> 4, i = lane & 15;
-  Pan<Q> pr;
-  load_row<Q>(z, bn + 4 * g, g);
-  if (!ch.ready) {
-    fetch_f<Q>(pr, Kn, 0);
-    put_f<Q>(buf + ch.ph * G::PSZ, pr);
-    __syncthreads();
-  }
-#pragma unroll
-  for (int p = 0; p < G::NP; ++p) {
-    const bool more = p + 1 < G::NP;
-    if (more) fetch_f<Q>(pr, Kn, p + 1);
-    else if (Knext) fetch_f<Q>(pr, Knext, 0);
-    const float* P = buf + ((ch.ph + p) & 1) * G::PSZ + i * G::PLF + 4 * g;
+  for (int m = 0; m < 2; ++m) {
+    const int o = 32 * w + 16 * m + i, oc = o < Q ? o : 0;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      // output blocks in two halves: half the A registers, still 7 independent chains
+      int k = k0 + 16 * h;
+      if (32 * (p + 1) > Q) k = 32 * p + k < Q ? k : 0;
+      const uint32_t off = 4u * (uint32_t)(TR ? k * Q + oc : oc * Q + k);
+      if constexpr (!TR) {
+        a.r[m][h] = *reinterpret_cast<const f32x4*>(base + off);
+      } else {
 #pragma unroll
-      for (int o0 = 0; o0 < NB; o0 += NB / 2) {
-        f32x4 av[NB / 2];
-#pragma unroll
-        for (int ob = 0; ob < NB / 2; ++ob)
-          av[ob] = *reinterpret_cast<const f32x4*>(P + 16 * (o0 + ob) * G::PLF + 16 * h);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int ob = 0; ob < NB / 2; ++ob)
-            z[o0 + ob] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ob][r], v[2 * p + h][r], z[o0 + ob], 0, 0, 0);
+        for (int t = 0; t < 4; ++t) a.r[m][h][t] = *reinterpret_cast<const float*>(base + t * 4 * Q + off);
       }
     }
-    if (more || Knext) put_f<Q>(buf + ((ch.ph + p + 1) & 1) * G::PSZ, pr);
-    __syncthreads();
   }
-  ch.ph = (ch.ph + G::NP) & 1;
-  ch.ready = Knext != nullptr;
 }
 
-// w = K_n^T s (same calling rules as prod). The next panel moves in two parts,
-// each fetched before half of the current panel's products and written after it,
-// so only half a panel is held in registers at a time.
-template <int Q>
-__device__ __forceinline__ void prod_t(f32x4 (&w)[Geo<Q>::NB], const f32x4 (&s)[Geo<Q>::NB],
-                                       const float* __restrict__ Kn, float* buf, int lane) {
-  using G = Geo<Q>;
-  constexpr int NB = G::NB, H1 = (G::PPT + 1) / 2;
-  const int g = lane >> 4, i = lane & 15;
-  {
-    f32x4 r0[H1], r1[G::PPT - H1];
-    fetch_a<Q, 0, H1>(r0, Kn, 0);
-    fetch_a<Q, H1, G::PPT>(r1, Kn, 0);
-    put_a<Q, 0, H1>(buf, r0);
-    put_a<Q, H1, G::PPT>(buf, r1);
+// Publishes the wave's values: split, panel w of every tile.
+template <int Q, int T>
+__device__ __forceinline__ void publish(bf16x8* sh, const Val<T>& v, const Ctx<Q, T>& c) {
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const Split8 f = split8(v[t][0], v[t][1]);
+#pragma unroll
+    for (int part = 0; part < 3; ++part) sh[((t * Geo<Q>::NP + c.w) * 3 + part) * 64 + c.lane] = f.p[part];
   }
+}
+
+// z += K_n v (or K_n^T v) for the published v. Two panels of weights are in flight;
+// q0, q1 hold panels 0 and 1 on entry and those of the next product (Knext, kind
+// NTR; nullptr: none) on return.
+template <int Q, int T, bool TR, bool NTR>
+__device__ __forceinline__ void prod(Val<T>& z, const float* __restrict__ Kn, const bf16x8* sh, const Ctx<Q, T>& c,
+                                     Raw& q0, Raw& q1, const float* __restrict__ Knext) {
+  constexpr int NP = Geo<Q>::NP;
+  const bf16x8* B = sh + c.lane;
 #pragma unroll
-  for (int ob = 0; ob < NB; ++ob) w[ob] = 0.f;
-  __syncthreads();
+  for (int p = 0; p < NP; ++p) {
+    Raw& q = p & 1 ? q1 : q0;
+    const Split8 a0 = split8(q.r[0][0], q.r[0][1]), a1 = split8(q.r[1][0], q.r[1][1]);
+    if (p + 2 < NP) fetch_a<Q, TR>(q, Kn, p + 2, c.w, c.lane);
 #pragma unroll
-  for (int p = 0; p < G::NP; ++p) {
-    const float* P = buf + (p & 1) * G::PSZ + 4 * g * G::PLA + i;
-    float* nxt = buf + ((p + 1) & 1) * G::PSZ;
+    for (int t = 0; t < T; t += 2) {
+      Split8 b[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      f32x4 r0[H1], r1[G::PPT - H1];
-      if (p + 1 < G::NP) {
-        if (h == 0) fetch_a<Q, 0, H1>(r0, Kn, p + 1);
-        else fetch_a<Q, H1, G::PPT>(r1, Kn, p + 1);
-      }
-      // output blocks in two halves, as in the forward product: 28 A values in
-      // registers, 7 independent accumulation chains
+      for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int o0 = 0; o0 < NB; o0 += NB / 2) {
-        float av[4][NB / 2];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int ob = 0; ob < NB / 2; ++ob) av[r][ob] = P[(16 * h + r) * G::PLA + 16 * (o0 + ob)];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int ob = 0; ob < NB / 2; ++ob)
-            w[o0 + ob] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r][ob], s[2 * p + h][r], w[o0 + ob], 0, 0, 0);
-      }
-      if (p + 1 < G::NP) {
-        if (h == 0) put_a<Q, 0, H1>(nxt, r0);
-        else put_a<Q, H1, G::PPT>(nxt, r1);
-      }
+        for (int part = 0; part < 3; ++part) b[u].p[part] = B[(((t + u) * NP + p) * 3 + part) * 64];
+      mma_split4(a0, a1, b[0], b[1], z[t][0], z[t][1], z[t + 1][0], z[t + 1][1]);
     }
-    __syncthreads();
+  }
+  if (Knext) {
+    fetch_a<Q, NTR>(q0, Knext, 0, c.w, c.lane);
+    fetch_a<Q, NTR>(q1, Knext, 1, c.w, c.lane);
   }
 }
 
@@ -369,22 +284,18 @@ __device__ __forceinline__ void xcd_item(int& tile, int& itv) {
 }
 
 // ------------------------------------------------------------------ forward
-template <int Q, int MODE, bool REC>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_fwd(SweepArgs a) {
+template <int Q, int MODE, bool REC, int T>
+__global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_fwd(SweepArgs a) {
   using G = Geo<Q>;
-  constexpr int NB = G::NB;
-  __shared__ __attribute__((aligned(16))) float buf[2 * G::PSZ];
-  __shared__ double red[WAVES];
-  const int lane = threadIdx.x & 63, g = lane >> 4;
+  __shared__ bf16x8 sh[T * G::NF];
+  __shared__ double red[G::NP];
   int tile, k;
   xcd_item(tile, k);
   const int Nc = gridDim.y;
-  const int e = (tile * WAVES + (threadIdx.x >> 6)) * EX + (lane & 15);
-  const bool on = e < a.B;
+  const Ctx<Q, T> cx(tile, a.B);
   const size_t slice = (size_t)a.B * Q;
-  const size_t row = (size_t)(on ? e : 0) * Q + 4 * g;
   const float* K = static_cast<const float*>(a.K);
-  const float* bb = static_cast<const float*>(a.b);
+  const float* bb = static_cast<const float*>(a.b) + 32 * cx.w + 4 * cx.g;
   float* X = static_cast<float*>(a.X);
   const float* Gr = static_cast<const float*>(a.G);
   const float* Cs = static_cast<const float*>(a.Cs);
@@ -393,144 +304,174 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   const int nsteps = MODE == MODE_SERIAL ? a.Nl : (MODE == SWEEP_CORRF ? c - 1 : c);
   const float hl = (float)a.hl, hc = (float)a.hc;
   const long kc = MODE == MODE_SERIAL ? 0 : (long)k * c;
+  auto layer = [&](long j) { return K + (size_t)(kc + j) * a.stride * (Q * Q); };
 
-  f32x4 v[NB];
-#pragma unroll
-  for (int mb = 0; mb < NB; ++mb) v[mb] = 0.f;
-  if (on) {
-    if (MODE == SWEEP_FC || MODE == MODE_SERIAL) {
-      // a pending coarse-grid correction of the previous cycle is applied on the fly
-      if (MODE == SWEEP_FC && Vn)
-        correct<Q>(v, Cs + (size_t)k * a.cs_stride * slice + row, Vn + (size_t)k * slice + row, g);
-      else load_row<Q>(v, X + kc * slice + row, g);
-      if (MODE == SWEEP_FC && k == 0) store_row<Q>(static_cast<float*>(a.S) + row, v, g);
-    } else if (MODE == SWEEP_FRES) {
-      load_row<Q>(v, Cs + (size_t)k * a.cs_stride * slice + row, g);
-    } else {
-      correct<Q>(v, Cs + (size_t)k * a.cs_stride * slice + row, Vn + (size_t)k * slice + row, g);
-      if (k > 0) store_row<Q>(X + kc * slice + row, v, g);
-    }
-  }
   // the final F-relaxation (and a level-0 serial solve) records sigma'(z) of every
   // layer; CORRF then also takes the product of the layer before the next C-point
   constexpr bool rec = REC && (MODE == SWEEP_CORRF || MODE == MODE_SERIAL);
+  constexpr bool extra = MODE == SWEEP_CORRF && rec;
+  Raw q0, q1;
+  if (nsteps > 0 || extra) {
+    fetch_a<Q, false>(q0, layer(0), 0, cx.w, cx.lane);
+    fetch_a<Q, false>(q1, layer(0), 1, cx.w, cx.lane);
+  }
+  Val<T> v;
+  if (MODE == SWEEP_FC || MODE == MODE_SERIAL) {
+    // a pending coarse-grid correction of the previous cycle is applied on the fly
+    if (MODE == SWEEP_FC && Vn) correct<Q, T>(v, Cs + (size_t)k * a.cs_stride * slice, Vn + (size_t)k * slice, cx);
+    else load_rows<Q, T>(v, X + kc * slice, cx);
+    if (MODE == SWEEP_FC && k == 0) store_rows<Q, T>(static_cast<float*>(a.S), v, cx);
+  } else if (MODE == SWEEP_FRES) {
+    load_rows<Q, T>(v, Cs + (size_t)k * a.cs_stride * slice, cx);
+  } else {
+    correct<Q, T>(v, Cs + (size_t)k * a.cs_stride * slice, Vn + (size_t)k * slice, cx);
+    if (k > 0) store_rows<Q, T>(X + kc * slice, v, cx);
+  }
+  publish<Q, T>(sh, v, cx);
+  __syncthreads();
   // FRES parks the coarse step's value v + h_c sigma(z) of the first layer in its
   // Gn row and finishes g_{l+1}^{k+1} = v - (that value) after the interval, so it
-  // holds no extra row of registers across the steps
-  float* gn = MODE == SWEEP_FRES ? static_cast<float*>(a.Gn) + (size_t)(k + 1) * slice + row : nullptr;
-  Chain ch;
+  // holds no extra registers across the steps
+  float* gn = MODE == SWEEP_FRES ? static_cast<float*>(a.Gn) + (size_t)(k + 1) * slice : nullptr;
+  auto product = [&](Val<T>& z, int j) {
+    const float* bn = bb + (size_t)(kc + j) * a.stride * Q;
+    f32x4 b2[2];
+    load2(b2, bn, cx.ok1);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      z[t][0] = b2[0];
+      z[t][1] = b2[1];
+    }
+    prod<Q, T, false, false>(z, layer(j), sh, cx, q0, q1, j + 1 < nsteps + (extra ? 1 : 0) ? layer(j + 1) : nullptr);
+  };
   for (int j = 0; j < nsteps; ++j) {
-    const size_t n = (size_t)(kc + j) * a.stride;
-    // the next product: the next step's layer, or CORRF's extra record product
-    const float* knext = j + 1 < nsteps                      ? K + (size_t)(kc + j + 1) * a.stride * (Q * Q)
-                         : (MODE == SWEEP_CORRF && rec) ? K + (size_t)(kc + nsteps) * a.stride * (Q * Q)
-                                                        : nullptr;
-    f32x4 z[NB];
-    prod<Q>(z, v, K + n * (Q * Q), bb + n * Q, buf, lane, ch, knext);
+    Val<T> z;
+    product(z, j);
     if constexpr (rec) {
-      f32x4 dz[NB];
+      Val<T> dz;
 #pragma unroll
-      for (int mb = 0; mb < NB; ++mb) dz[mb] = z[mb];
-      apply<Q>(dz, a.act, true, g);
-      if (on) store_dsig<Q>(a.dsig, n * slice + row, a.act, dz, g);
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) dz[t][m] = z[t][m];
+      apply<true, T>(dz, a.act, cx.ok1);
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+        if (cx.on[t]) store_dsig(a.dsig, (size_t)(kc + j) * a.stride * slice + cx.row[t], a.act, dz[t], cx.ok1);
     }
-    apply<Q>(z, a.act, false, g);
-    if (MODE == SWEEP_FRES && j == 0 && on) {
-      f32x4 coarse[NB];
+    apply<false, T>(z, a.act, cx.ok1);
 #pragma unroll
-      for (int mb = 0; mb < NB; ++mb) coarse[mb] = v[mb] + hc * z[mb];
-      store_row<Q>(gn, coarse, g);
-    }
-#pragma unroll
-    for (int mb = 0; mb < NB; ++mb) v[mb] = v[mb] + hl * z[mb];
-    if (on) {
-      if (Gr) {
-        f32x4 t[NB];
-        load_row<Q>(t, Gr + (kc + j + 1) * slice + row, g);
-#pragma unroll
-        for (int mb = 0; mb < NB; ++mb) v[mb] += t[mb];
+    for (int t = 0; t < T; ++t) {
+      if (MODE == SWEEP_FRES && j == 0 && cx.on[t]) {
+        const f32x4 cs[2] = {v[t][0] + hc * z[t][0], v[t][1] + hc * z[t][1]};
+        store2(gn + cx.row[t], cs, cx.ok1);
       }
-      if (MODE == SWEEP_CORRF || MODE == MODE_SERIAL) store_row<Q>(X + (kc + j + 1) * slice + row, v, g);
+#pragma unroll
+      for (int m = 0; m < 2; ++m) v[t][m] = v[t][m] + hl * z[t][m];
+      if (Gr) {
+        f32x4 gv[2];
+        load2(gv, Gr + (kc + j + 1) * slice + cx.row[t], cx.ok1);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) v[t][m] += gv[m];
+      }
+    }
+    if (MODE == SWEEP_CORRF || MODE == MODE_SERIAL) store_rows<Q, T>(X + (kc + j + 1) * slice, v, cx);
+    if (j + 1 < nsteps || extra) {
+      __syncthreads();  // every read of the old state is done
+      publish<Q, T>(sh, v, cx);
+      __syncthreads();
     }
   }
-  if constexpr (MODE == SWEEP_CORRF && rec) {
+  if constexpr (extra) {
     // sigma' of the layer before the next C-point, from the last F-point
-    const size_t n = (size_t)(kc + nsteps) * a.stride;
-    f32x4 z[NB];
-    prod<Q>(z, v, K + n * (Q * Q), bb + n * Q, buf, lane, ch);
-    apply<Q>(z, a.act, true, g);
-    if (on) store_dsig<Q>(a.dsig, n * slice + row, a.act, z, g);
+    Val<T> z;
+    product(z, nsteps);
+    apply<true, T>(z, a.act, cx.ok1);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      if (cx.on[t]) store_dsig(a.dsig, (size_t)(kc + nsteps) * a.stride * slice + cx.row[t], a.act, z[t], cx.ok1);
   }
   if (MODE == SWEEP_FC) {
-    if (on) store_row<Q>(static_cast<float*>(a.S) + (size_t)(k + 1) * slice + row, v, g);
+    store_rows<Q, T>(static_cast<float*>(a.S) + (size_t)(k + 1) * slice, v, cx);
   } else if (MODE == SWEEP_FRES) {
     double acc = 0.0;
-    if (on) {
-      f32x4 cn[NB], coarse[NB];
-      load_row<Q>(cn, Cs + (size_t)(k + 1) * a.cs_stride * slice + row, g);
-      acc = sq_diff<Q>(v, cn);
-      load_row<Q>(coarse, gn, g);
+    const float* cn = Cs + (size_t)(k + 1) * a.cs_stride * slice;
 #pragma unroll
-      for (int mb = 0; mb < NB; ++mb) coarse[mb] = v[mb] - coarse[mb];  // g_{l+1}^{k+1}
-      store_row<Q>(gn, coarse, g);
+    for (int t = 0; t < T; ++t) {
+      if (!cx.on[t]) continue;
+      f32x4 x[2], cs[2];
+      load2(x, cn + cx.row[t], cx.ok1);
+      load2(cs, gn + cx.row[t], cx.ok1);
+      acc += sq_diff(v[t], x);
+#pragma unroll
+      for (int m = 0; m < 2; ++m) cs[m] = v[t][m] - cs[m];  // g_{l+1}^{k+1}
+      store2(gn + cx.row[t], cs, cx.ok1);
       if (a.xn_every > 0 && (k + 1) % a.xn_every == 0)
-        store_row<Q>(static_cast<float*>(a.Xn) + (size_t)(k + 1) * slice + row, cn, g);
+        store2(static_cast<float*>(a.Xn) + (size_t)(k + 1) * slice + cx.row[t], x, cx.ok1);
       if (k == 0) {
-        load_row<Q>(cn, Cs + row, g);
-        store_row<Q>(static_cast<float*>(a.Xn) + row, cn, g);
+        load2(x, Cs + cx.row[t], cx.ok1);
+        store2(static_cast<float*>(a.Xn) + cx.row[t], x, cx.ok1);
       }
     }
     if (a.partial) {
-      const double s = wg_sum(acc, red);
+      const double s = wg_sum<G::NP>(acc, red);
       if (threadIdx.x == 0) a.partial[(size_t)k * gridDim.x + tile] = s;
     }
   } else if (MODE == SWEEP_CORRF) {
-    if (on && k == Nc - 1) {
-      correct<Q>(v, Cs + (size_t)Nc * a.cs_stride * slice + row, Vn + (size_t)Nc * slice + row, g);
-      store_row<Q>(X + (size_t)a.Nl * slice + row, v, g);
+    if (k == Nc - 1) {
+      correct<Q, T>(v, Cs + (size_t)Nc * a.cs_stride * slice, Vn + (size_t)Nc * slice, cx);
+      store_rows<Q, T>(X + (size_t)a.Nl * slice, v, cx);
     }
   }
 }
 
-// sigma'(K_n u^n + b_n) of the fine state n: from the record, or by the forward
-// product (every thread calls it: the product holds barriers)
-template <int Q, bool REC>
-__device__ __forceinline__ void sigma_prime(f32x4 (&d)[Geo<Q>::NB], const SweepArgs& a, size_t n, size_t slice,
-                                            size_t row, bool on, float* buf, int lane) {
-  constexpr int NB = Geo<Q>::NB;
-  const int g = lane >> 4;
+// s = sigma'(K_n u^n + b_n) * v of the fine state n, published: sigma' from the
+// record, or by the forward product (whose weights q0, q1 hold on entry; on return
+// they hold the transposed product's). Holds barriers; the caller's reads of sh are
+// done.
+template <int Q, bool REC, int T>
+__device__ __forceinline__ void publish_s(const Val<T>& v, const SweepArgs& a, size_t n, size_t slice, bf16x8* sh,
+                                          const Ctx<Q, T>& cx, Raw& q0, Raw& q1) {
+  Val<T> d;
   if constexpr (REC) {
-    // every lane reads a valid row; values of lanes past the batch are never stored
-    load_dsig<Q>(d, a.dsig, n * slice + row, a.act, g);
-  } else {
-    f32x4 u[NB];
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) u[mb] = 0.f;
-    if (on) load_row<Q>(u, static_cast<const float*>(a.Uf) + n * slice + row, g);
-    Chain own;  // loads its own first panel
-    prod<Q>(d, u, static_cast<const float*>(a.K) + n * (Q * Q), static_cast<const float*>(a.b) + n * Q, buf, lane,
-            own);
-    apply<Q>(d, a.act, true, g);
+    for (int t = 0; t < T; ++t) load_dsig(d[t], a.dsig, n * slice + cx.row[t], a.act, cx.ok1);
+  } else {
+    const float* Kn = static_cast<const float*>(a.K) + n * (Q * Q);
+    load_rows<Q, T>(d, static_cast<const float*>(a.Uf) + n * slice, cx);
+    publish<Q, T>(sh, d, cx);
+    __syncthreads();
+    f32x4 b2[2];
+    load2(b2, static_cast<const float*>(a.b) + n * Q + 32 * cx.w + 4 * cx.g, cx.ok1);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      d[t][0] = b2[0];
+      d[t][1] = b2[1];
+    }
+    prod<Q, T, false, true>(d, Kn, sh, cx, q0, q1, Kn);
+    apply<true, T>(d, a.act, cx.ok1);
+    __syncthreads();
   }
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int m = 0; m < 2; ++m) d[t][m] = d[t][m] * v[t][m];
+  publish<Q, T>(sh, d, cx);
+  __syncthreads();
 }
 
 // ------------------------------------------------------------------ adjoint
 // Interval k runs from its upper C-point (k+1)c down to kc; step j produces level
 // point i = (k+1)c-1-j, linearised at the fine state of index i*stride.
-template <int Q, int MODE, bool REC>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_adj(SweepArgs a) {
+template <int Q, int MODE, bool REC, int T>
+__global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_adj(SweepArgs a) {
   using G = Geo<Q>;
-  constexpr int NB = G::NB;
-  __shared__ __attribute__((aligned(16))) float buf[2 * G::PSZ];
-  __shared__ double red[WAVES];
-  const int lane = threadIdx.x & 63, g = lane >> 4;
+  __shared__ bf16x8 sh[T * G::NF];
+  __shared__ double red[G::NP];
   int tile, k;
   xcd_item(tile, k);
   const int Nc = gridDim.y;
-  const int e = (tile * WAVES + (threadIdx.x >> 6)) * EX + (lane & 15);
-  const bool on = e < a.B;
+  const Ctx<Q, T> cx(tile, a.B);
   const size_t slice = (size_t)a.B * Q;
-  const size_t row = (size_t)(on ? e : 0) * Q + 4 * g;
   const float* K = static_cast<const float*>(a.K);
   float* X = static_cast<float*>(a.X);
   const float* Gr = static_cast<const float*>(a.G);
@@ -540,44 +481,51 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   const int nsteps = MODE == MODE_SERIAL ? a.Nl : (MODE == SWEEP_CORRF ? c - 1 : c);
   const float hl = (float)a.hl, hc = (float)a.hc;
   const long top = MODE == MODE_SERIAL ? (long)a.Nl : (long)(k + 1) * c;
+  auto layer = [&](long j) { return K + (size_t)(top - 1 - j) * a.stride * (Q * Q); };
 
-  f32x4 v[NB];
-#pragma unroll
-  for (int mb = 0; mb < NB; ++mb) v[mb] = 0.f;
-  if (on) {
-    if (MODE == SWEEP_FC || MODE == MODE_SERIAL) {
-      if (MODE == SWEEP_FC && Vn)
-        correct<Q>(v, Cs + (size_t)(k + 1) * a.cs_stride * slice + row, Vn + (size_t)(k + 1) * slice + row, g);
-      else load_row<Q>(v, X + top * slice + row, g);
-      if (MODE == SWEEP_FC && k == Nc - 1) store_row<Q>(static_cast<float*>(a.S) + (size_t)Nc * slice + row, v, g);
-    } else if (MODE == SWEEP_FRES) {
-      load_row<Q>(v, Cs + (size_t)(k + 1) * a.cs_stride * slice + row, g);
-    } else {
-      correct<Q>(v, Cs + (size_t)(k + 1) * a.cs_stride * slice + row, Vn + (size_t)(k + 1) * slice + row, g);
-      if (k + 1 < Nc) store_row<Q>(X + top * slice + row, v, g);
-    }
+  Raw q0, q1;
+  if (nsteps > 0) {
+    fetch_a<Q, REC>(q0, layer(0), 0, cx.w, cx.lane);
+    fetch_a<Q, REC>(q1, layer(0), 1, cx.w, cx.lane);
   }
-  double acc = 0.0;  // FRES: squared residual of the lower C-point
+  Val<T> v;
+  if (MODE == SWEEP_FC || MODE == MODE_SERIAL) {
+    if (MODE == SWEEP_FC && Vn)
+      correct<Q, T>(v, Cs + (size_t)(k + 1) * a.cs_stride * slice, Vn + (size_t)(k + 1) * slice, cx);
+    else load_rows<Q, T>(v, X + top * slice, cx);
+    if (MODE == SWEEP_FC && k == Nc - 1) store_rows<Q, T>(static_cast<float*>(a.S) + (size_t)Nc * slice, v, cx);
+  } else if (MODE == SWEEP_FRES) {
+    load_rows<Q, T>(v, Cs + (size_t)(k + 1) * a.cs_stride * slice, cx);
+  } else {
+    correct<Q, T>(v, Cs + (size_t)(k + 1) * a.cs_stride * slice, Vn + (size_t)(k + 1) * slice, cx);
+    if (k + 1 < Nc) store_rows<Q, T>(X + top * slice, v, cx);
+  }
   for (int j = 0; j < nsteps; ++j) {
     const long i = top - 1 - j;
     const size_t n = (size_t)i * a.stride;
-    f32x4 d[NB], w[NB];
-    sigma_prime<Q, REC>(d, a, n, slice, row, on, buf, lane);
+    publish_s<Q, REC, T>(v, a, n, slice, sh, cx, q0, q1);
+    Val<T> w;
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) d[mb] = d[mb] * v[mb];
-    prod_t<Q>(w, d, K + n * (Q * Q), buf, lane);
+    for (int t = 0; t < T; ++t) w[t][0] = w[t][1] = 0.f;
+    // the next product: the next step's first one, or the coarse step's with the same weights
+    const float* next = j + 1 < nsteps ? layer(j + 1) : MODE == SWEEP_FRES ? layer(j) : nullptr;
+    prod<Q, T, true, REC>(w, layer(j), sh, cx, q0, q1, next);
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) v[mb] = v[mb] + hl * w[mb];
-    if (on) {
+    for (int t = 0; t < T; ++t) {
+      if (!cx.ok1) w[t][1] = 0.f;
+#pragma unroll
+      for (int m = 0; m < 2; ++m) v[t][m] = v[t][m] + hl * w[t][m];
       if (Gr) {
-        f32x4 t[NB];
-        load_row<Q>(t, Gr + (size_t)i * slice + row, g);
+        f32x4 gv[2];
+        load2(gv, Gr + (size_t)i * slice + cx.row[t], cx.ok1);
 #pragma unroll
-        for (int mb = 0; mb < NB; ++mb) v[mb] += t[mb];
+        for (int m = 0; m < 2; ++m) v[t][m] += gv[m];
       }
-      if (MODE == SWEEP_CORRF || MODE == MODE_SERIAL) store_row<Q>(X + (size_t)i * slice + row, v, g);
     }
+    if (MODE == SWEEP_CORRF || MODE == MODE_SERIAL) store_rows<Q, T>(X + (size_t)i * slice, v, cx);
+    __syncthreads();  // every read of s is done
   }
+  double acc = 0.0;  // FRES: squared residual of the lower C-point
   if constexpr (MODE == SWEEP_FRES) {
     // coarse adjoint step from the upper C-point, linearised at the fine state of
     // the interval's last step (sigma' is taken again: same operands, same
@@ -590,52 +538,50 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     // The residual of the lower C-point is taken first and v is parked in its Gn
     // row, so the state's registers are free during the coarse product.
     const size_t n = (size_t)(top - nsteps) * a.stride;
-    float* gn = static_cast<float*>(a.Gn) + (size_t)k * slice + row;
-    const float* cup = Cs + (size_t)(k + 1) * a.cs_stride * slice + row;
-    if (on) {
-      f32x4 ck[NB];
-      load_row<Q>(ck, Cs + (size_t)k * a.cs_stride * slice + row, g);
-      acc = sq_diff<Q>(v, ck);
+    float* gn = static_cast<float*>(a.Gn) + (size_t)k * slice;
+    const float* cup = Cs + (size_t)(k + 1) * a.cs_stride * slice;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      if (!cx.on[t]) continue;
+      f32x4 x[2];
+      load2(x, Cs + (size_t)k * a.cs_stride * slice + cx.row[t], cx.ok1);
+      acc += sq_diff(v[t], x);
       if (a.xn_every > 0 && k % a.xn_every == 0)
-        store_row<Q>(static_cast<float*>(a.Xn) + (size_t)k * slice + row, ck, g);
+        store2(static_cast<float*>(a.Xn) + (size_t)k * slice + cx.row[t], x, cx.ok1);
       if (k == Nc - 1) {
-        load_row<Q>(ck, Cs + (size_t)Nc * a.cs_stride * slice + row, g);
-        store_row<Q>(static_cast<float*>(a.Xn) + (size_t)Nc * slice + row, ck, g);
+        load2(x, Cs + (size_t)Nc * a.cs_stride * slice + cx.row[t], cx.ok1);
+        store2(static_cast<float*>(a.Xn) + (size_t)Nc * slice + cx.row[t], x, cx.ok1);
       }
-      store_row<Q>(gn, v, g);
+      store2(gn + cx.row[t], v[t], cx.ok1);
     }
-    f32x4 d[NB], w[NB], t[NB];
-    sigma_prime<Q, REC>(d, a, n, slice, row, on, buf, lane);
+    load_rows<Q, T>(v, cup, cx);
+    publish_s<Q, REC, T>(v, a, n, slice, sh, cx, q0, q1);
+    Val<T> w;
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) {
-      t[mb] = 0.f;
-      w[mb] = 0.f;
-    }
-    if (on) load_row<Q>(t, cup, g);
+    for (int t = 0; t < T; ++t) w[t][0] = w[t][1] = 0.f;
+    prod<Q, T, true, true>(w, K + n * (Q * Q), sh, cx, q0, q1, nullptr);
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) d[mb] = d[mb] * t[mb];
-    prod_t<Q>(w, d, K + n * (Q * Q), buf, lane);
-    if (on) {
-      f32x4 vl[NB];
-      load_row<Q>(t, cup, g);
-      load_row<Q>(vl, gn, g);
+    for (int t = 0; t < T; ++t) {
+      if (!cx.on[t]) continue;
+      f32x4 x[2];
+      load2(x, gn + cx.row[t], cx.ok1);
 #pragma unroll
-      for (int mb = 0; mb < NB; ++mb) t[mb] = vl[mb] - (t[mb] + hc * w[mb]);  // g_{l+1}^k
-      store_row<Q>(gn, t, g);
+      for (int m = 0; m < 2; ++m) x[m] = x[m] - (v[t][m] + hc * w[t][m]);  // g_{l+1}^k
+      store2(gn + cx.row[t], x, cx.ok1);
     }
   }
 
   if (MODE == SWEEP_FC) {
-    if (on) store_row<Q>(static_cast<float*>(a.S) + (size_t)k * slice + row, v, g);
+    store_rows<Q, T>(static_cast<float*>(a.S) + (size_t)k * slice, v, cx);
   } else if (MODE == SWEEP_FRES) {
     if (a.partial) {
-      const double s = wg_sum(acc, red);
+      const double s = wg_sum<G::NP>(acc, red);
       if (threadIdx.x == 0) a.partial[(size_t)k * gridDim.x + tile] = s;
     }
   } else if (MODE == SWEEP_CORRF) {
-    if (on && k == 0) {
-      correct<Q>(v, Cs + row, Vn + row, g);
-      store_row<Q>(X + row, v, g);
+    if (k == 0) {
+      correct<Q, T>(v, Cs, Vn, cx);
+      store_rows<Q, T>(X, v, cx);
     }
   }
 }
@@ -644,90 +590,84 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // Workgroup (layer n, batch tile): the state residual Phi_n(u^n) - u^{n+1} or the
 // adjoint residual lam^{n+1} + h K_n^T (sigma'(K_n u^n + b_n) * lam^{n+1}) - lam^n,
 // squared and summed in fp64.
-template <int Q, int DIR>
-__global__ __launch_bounds__(NT) void k_resid(ResidArgs a) {
+template <int Q, int DIR, int T>
+__global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_resid(ResidArgs a) {
   using G = Geo<Q>;
-  constexpr int NB = G::NB;
-  __shared__ __attribute__((aligned(16))) float buf[2 * G::PSZ];
-  __shared__ double red[WAVES];
-  const int lane = threadIdx.x & 63, g = lane >> 4;
+  __shared__ bf16x8 sh[T * G::NF];
+  __shared__ double red[G::NP];
   const int n = blockIdx.x;
-  const int e = (blockIdx.y * WAVES + (threadIdx.x >> 6)) * EX + (lane & 15);
-  const bool on = e < a.B;
+  const Ctx<Q, T> cx(blockIdx.y, a.B);
   const size_t slice = (size_t)a.B * Q;
-  const size_t row = (size_t)(on ? e : 0) * Q + 4 * g;
   const float* U = static_cast<const float*>(a.U);
   const float* L = static_cast<const float*>(a.Lam);
   const float* Kn = static_cast<const float*>(a.K) + (size_t)n * (Q * Q);
-  const float* bn = static_cast<const float*>(a.b) + (size_t)n * Q;
   const float h = (float)a.h;
-  f32x4 v[NB], z[NB];
+  Raw q0, q1;
+  fetch_a<Q, false>(q0, Kn, 0, cx.w, cx.lane);
+  fetch_a<Q, false>(q1, Kn, 1, cx.w, cx.lane);
+  Val<T> v, z;
+  load_rows<Q, T>(v, U + (size_t)n * slice, cx);
+  publish<Q, T>(sh, v, cx);
+  __syncthreads();
+  f32x4 b2[2];
+  load2(b2, static_cast<const float*>(a.b) + (size_t)n * Q + 32 * cx.w + 4 * cx.g, cx.ok1);
 #pragma unroll
-  for (int mb = 0; mb < NB; ++mb) v[mb] = 0.f;
-  if (on) load_row<Q>(v, U + (size_t)n * slice + row, g);
-  Chain ch;
-  prod<Q>(z, v, Kn, bn, buf, lane, ch);
-  double acc = 0.0;
-  if constexpr (DIR == DIR_FWD) {
-    apply<Q>(z, a.act, false, g);
-    if (on) {
-      f32x4 nx[NB];
-      load_row<Q>(nx, U + (size_t)(n + 1) * slice + row, g);
-#pragma unroll
-      for (int mb = 0; mb < NB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float d = (v[mb][r] + h * z[mb][r]) - nx[mb][r];
-          acc += (double)d * (double)d;
-        }
-    }
-  } else {
-    apply<Q>(z, a.act, true, g);
-    f32x4 lam[NB], w[NB];
-#pragma unroll
-    for (int mb = 0; mb < NB; ++mb) lam[mb] = 0.f;
-    if (on) load_row<Q>(lam, L + (size_t)(n + 1) * slice + row, g);
-#pragma unroll
-    for (int mb = 0; mb < NB; ++mb) z[mb] = z[mb] * lam[mb];
-    prod_t<Q>(w, z, Kn, buf, lane);
-    if (on) {
-      load_row<Q>(v, L + (size_t)n * slice + row, g);
-#pragma unroll
-      for (int mb = 0; mb < NB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float d = (lam[mb][r] + h * w[mb][r]) - v[mb][r];
-          acc += (double)d * (double)d;
-        }
-    }
+  for (int t = 0; t < T; ++t) {
+    z[t][0] = b2[0];
+    z[t][1] = b2[1];
   }
-  const double s = wg_sum(acc, red);
+  prod<Q, T, false, true>(z, Kn, sh, cx, q0, q1, DIR == DIR_ADJ ? Kn : nullptr);
+  const float* next = DIR == DIR_FWD ? U + (size_t)(n + 1) * slice : L + (size_t)n * slice;
+  if constexpr (DIR == DIR_FWD) {
+    apply<false, T>(z, a.act, cx.ok1);
+  } else {
+    apply<true, T>(z, a.act, cx.ok1);
+    load_rows<Q, T>(v, L + (size_t)(n + 1) * slice, cx);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int m = 0; m < 2; ++m) z[t][m] = z[t][m] * v[t][m];
+    __syncthreads();
+    publish<Q, T>(sh, z, cx);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < T; ++t) z[t][0] = z[t][1] = 0.f;
+    prod<Q, T, true, true>(z, Kn, sh, cx, q0, q1, nullptr);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      if (!cx.ok1) z[t][1] = 0.f;
+  }
+  double acc = 0.0;
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    if (!cx.on[t]) continue;
+    f32x4 x[2], f[2];
+    load2(x, next + cx.row[t], cx.ok1);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) f[m] = v[t][m] + h * z[t][m];
+    acc += sq_diff(f, x);
+  }
+  const double s = wg_sum<G::NP>(acc, red);
   if (threadIdx.x == 0) a.partial[(size_t)blockIdx.x * gridDim.y + blockIdx.y] = s;
 }
 
 // ------------------------------------------------------------------ gradient
-// Workgroup (layer n, batch chunk), 64 examples at a time: each wave forms
-// s = sigma'(z) * lam^{n+1} for its 16 examples (sigma' from the record, or from
-// the forward product), then s and u pass through LDS as [example][feature]
-// tiles, 32 examples at a time, and dK[i][j] += sum_e s[e][i] u[e][j] runs on
-// v_mfma_f32_32x32x2_f32 with the examples as the contraction index (k-slice t
-// pairs examples 2t and 2t+1). The 7 x 7 output blocks of 32 x 32 are dealt to
-// the four waves (block b to wave b % 4), so no cross-wave reduction is needed;
-// db sums the s tile's columns. A second pass sums the chunk partials in order
-// and scales by h.
+// Workgroup (layer n, batch chunk), GT tiles (64 examples) at a time: the waves form
+// s = sigma'(z) * lam^{n+1} (sigma' from the record, or from the forward product),
+// then s and u pass through LDS as [example][feature] tiles, 32 examples at a time,
+// and dK[i][j] += sum_e s[e][i] u[e][j] runs on v_mfma_f32_32x32x2_f32 with the
+// examples as the contraction index (k-slice t pairs examples 2t and 2t+1). The 7 x 7
+// output blocks of 32 x 32 are dealt to the seven waves, a row of blocks each, so no
+// cross-wave reduction is needed; db sums the s tile's columns. A second pass sums
+// the chunk partials in order and scales by h.
+constexpr int GT = 4;
 template <int Q, bool REC>
-__global__ __launch_bounds__(NT) void k_grad(GradArgs a) {
+__global__ __launch_bounds__(Geo<Q>::NT) void k_grad(GradArgs a) {
   using G = Geo<Q>;
-  constexpr int NB = G::NB, QP = G::QP;
-  constexpr int OB = QP / 32;            // 32-row output blocks per side
-  constexpr int NOB = OB * OB;
-  constexpr int MAXB = (NOB + WAVES - 1) / WAVES;
-  constexpr int TL = QP;                 // tile pitch: rows 2t and 2t+1 on disjoint banks (QP = 32 mod 64)
-  constexpr int PB = REC ? 1 : 2 * G::PSZ;
+  constexpr int NP = G::NP, TL = G::QP;  // tile pitch: rows 2t and 2t+1 on disjoint banks (QP = 32 mod 64)
   __shared__ __attribute__((aligned(16))) float tiles[2][32 * TL];
-  __shared__ __attribute__((aligned(16))) float buf[PB];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = lane >> 4, hh = lane >> 5, li = lane & 31;
+  __shared__ bf16x8 sh[REC ? 1 : GT * G::NF];
+  const int lane = threadIdx.x & 63, hh = lane >> 5, li = lane & 31;
   const int n = blockIdx.x, chunk = blockIdx.y;
   const int per = (((a.B + a.nchunks - 1) / a.nchunks) + 64 - 1) / 64 * 64;
   const int e0 = chunk * per, e1 = min(a.B, e0 + per);
@@ -735,61 +675,63 @@ __global__ __launch_bounds__(NT) void k_grad(GradArgs a) {
   const float* U = static_cast<const float*>(a.U) + (size_t)n * slice;
   const float* L = static_cast<const float*>(a.Lam) + (size_t)(n + 1) * slice;
   const float* Kn = static_cast<const float*>(a.K) + (size_t)n * (Q * Q);
-  const float* bn = static_cast<const float*>(a.b) + (size_t)n * Q;
-  f32x16 acc[MAXB];
+  f32x16 acc[NP];
 #pragma unroll
-  for (int b = 0; b < MAXB; ++b) acc[b] = 0.f;
+  for (int b = 0; b < NP; ++b) acc[b] = 0.f;
   float dbacc = 0.f;  // thread t < Q: column sum of s
-  int xo[MAXB], yo[MAXB];  // this wave's output blocks: row and column offsets
-#pragma unroll
-  for (int b = 0; b < MAXB; ++b) {
-    const int ob = wave + WAVES * b;
-    xo[b] = 32 * (ob / OB);
-    yo[b] = 32 * (ob % OB);
-  }
   float* st = tiles[0];
   float* ut = tiles[1];
-  for (int base = e0; base < e1; base += 64) {
-    const int e = base + wave * EX + (lane & 15);
-    const bool on = e < e1;
-    const size_t row = (size_t)(on ? e : 0) * Q + 4 * g;
-    f32x4 u[NB], s[NB], d[NB];
-#pragma unroll
-    for (int mb = 0; mb < NB; ++mb) u[mb] = 0.f;
-    if (on) load_row<Q>(u, U + row, g);
+  for (int base = e0; base < e1; base += 16 * GT) {
+    const Ctx<Q, GT> cx(base / (16 * GT), e1);
+    Val<GT> u, s;
+    load_rows<Q, GT>(u, U, cx);
     if constexpr (REC) {
-      load_dsig<Q>(d, a.dsig, (size_t)n * slice + row, a.act, g);
+#pragma unroll
+      for (int t = 0; t < GT; ++t) load_dsig(s[t], a.dsig, (size_t)n * slice + cx.row[t], a.act, cx.ok1);
     } else {
-      Chain own;  // loads its own first panel
-      prod<Q>(d, u, Kn, bn, buf, lane, own);
-      apply<Q>(d, a.act, true, g);
+      Raw q0, q1;
+      fetch_a<Q, false>(q0, Kn, 0, cx.w, cx.lane);
+      fetch_a<Q, false>(q1, Kn, 1, cx.w, cx.lane);
+      publish<Q, GT>(sh, u, cx);
+      __syncthreads();
+      f32x4 b2[2];
+      load2(b2, static_cast<const float*>(a.b) + (size_t)n * Q + 32 * cx.w + 4 * cx.g, cx.ok1);
+#pragma unroll
+      for (int t = 0; t < GT; ++t) {
+        s[t][0] = b2[0];
+        s[t][1] = b2[1];
+      }
+      prod<Q, GT, false, false>(s, Kn, sh, cx, q0, q1, nullptr);
+      apply<true, GT>(s, a.act, cx.ok1);
     }
-    // lam^{n+1} is loaded after the product, which needs the registers
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) s[mb] = 0.f;
-    if (on) load_row<Q>(s, L + row, g);
+    for (int t = 0; t < GT; ++t) {
+      f32x4 l[2];
+      load2(l, L + cx.row[t], cx.ok1);
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) s[mb] = d[mb] * s[mb];
-    // two halves of 32 examples: waves 0-1, then waves 2-3 fill the tiles
+      for (int m = 0; m < 2; ++m) {
+        s[t][m] = cx.on[t] ? s[t][m] * l[m] : f32x4{};
+        u[t][m] = cx.on[t] ? u[t][m] : f32x4{};
+      }
+    }
+    // two halves of 32 examples
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      if ((wave >> 1) == half) {
-        const int er = (wave & 1) * EX + (lane & 15);
 #pragma unroll
-        for (int mb = 0; mb < NB; ++mb) {
-          *reinterpret_cast<f32x4*>(st + er * TL + 16 * mb + 4 * g) = s[mb];
-          *reinterpret_cast<f32x4*>(ut + er * TL + 16 * mb + 4 * g) = u[mb];
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const int o = (16 * t + (lane & 15)) * TL + 32 * cx.w + 16 * m + 4 * cx.g;
+          *reinterpret_cast<f32x4*>(st + o) = s[2 * half + t][m];
+          *reinterpret_cast<f32x4*>(ut + o) = u[2 * half + t][m];
         }
-      }
       __syncthreads();
 #pragma unroll 4
       for (int t = 0; t < 16; ++t) {
-        const float* sr = st + (2 * t + hh) * TL + li;
+        const float sv = st[(2 * t + hh) * TL + 32 * cx.w + li];
         const float* ur = ut + (2 * t + hh) * TL + li;
 #pragma unroll
-        for (int b = 0; b < MAXB; ++b)
-          if (wave + WAVES * b < NOB)
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(sr[xo[b]], ur[yo[b]], acc[b], 0, 0, 0);
+        for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(sv, ur[32 * b], acc[b], 0, 0, 0);
       }
       if (threadIdx.x < Q)
         for (int t = 0; t < 32; ++t) dbacc += st[t * TL + threadIdx.x];
@@ -797,14 +739,13 @@ __global__ __launch_bounds__(NT) void k_grad(GradArgs a) {
     }
   }
   float* out = static_cast<float*>(a.partial) + ((size_t)n * a.nchunks + chunk) * (Q * Q + Q);
+  const int w = threadIdx.x >> 6;
 #pragma unroll
-  for (int b = 0; b < MAXB; ++b) {
-    const int ob = wave + WAVES * b;
-    if (ob >= NOB) continue;
-    const int j = 32 * (ob % OB) + li;
+  for (int b = 0; b < NP; ++b) {
+    const int j = 32 * b + li;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int i = 32 * (ob / OB) + 8 * (r >> 2) + 4 * hh + (r & 3);
+      const int i = 32 * w + 8 * (r >> 2) + 4 * hh + (r & 3);
       if (i < Q && j < Q) out[(size_t)i * Q + j] = acc[b][r];
     }
   }
@@ -826,33 +767,46 @@ __global__ __launch_bounds__(256) void k_grad_final(GradArgs a, int nw, int nbia
 }
 
 // ------------------------------------------------------------------ launchers
+template <int Q, int T>
+void sweep_t(int dir, const SweepArgs& a, dim3 grid, hipStream_t st) {
+  constexpr int NT = Geo<Q>::NT;
+  const bool rec = a.dsig != nullptr;
+  if (dir == DIR_FWD) {
+    // only the final F-relaxation (or a level-0 serial solve) writes the sigma' record
+    if (a.mode == SWEEP_FC) launch(k_fwd<Q, SWEEP_FC, false, T>, grid, NT, 0, st, a);
+    else if (a.mode == SWEEP_FRES) launch(k_fwd<Q, SWEEP_FRES, false, T>, grid, NT, 0, st, a);
+    else if (rec) launch(k_fwd<Q, SWEEP_CORRF, true, T>, grid, NT, 0, st, a);
+    else launch(k_fwd<Q, SWEEP_CORRF, false, T>, grid, NT, 0, st, a);
+  } else if (rec) {
+    if (a.mode == SWEEP_FC) launch(k_adj<Q, SWEEP_FC, true, T>, grid, NT, 0, st, a);
+    else if (a.mode == SWEEP_FRES) launch(k_adj<Q, SWEEP_FRES, true, T>, grid, NT, 0, st, a);
+    else launch(k_adj<Q, SWEEP_CORRF, true, T>, grid, NT, 0, st, a);
+  } else {
+    if (a.mode == SWEEP_FC) launch(k_adj<Q, SWEEP_FC, false, T>, grid, NT, 0, st, a);
+    else if (a.mode == SWEEP_FRES) launch(k_adj<Q, SWEEP_FRES, false, T>, grid, NT, 0, st, a);
+    else launch(k_adj<Q, SWEEP_CORRF, false, T>, grid, NT, 0, st, a);
+  }
+}
+
+// Six tiles per workgroup amortise a layer's weights best; with fewer workgroups than
+// that gives two rounds of the 256 CUs, four or two tiles per workgroup finish sooner.
 template <int Q>
 hipError_t sweep(int dir, const SweepArgs& a, hipStream_t st, int* partials) {
   const long Nc = a.Nl / a.c;
   if (Nc > 65535) return hipErrorNotSupported;  // intervals index the grid's y dimension
-  const dim3 grid((a.B + EX * WAVES - 1) / (EX * WAVES), (unsigned)Nc);
+  auto groups = [&](int T) { return (a.B + 16 * T - 1) / (16 * T); };
+  const int T = groups(6) * Nc >= 512 ? 6 : groups(4) * Nc >= 256 ? 4 : 2;
+  const dim3 grid(groups(T), (unsigned)Nc);
   if (partials) *partials = (int)(grid.x * grid.y);
-  const bool rec = a.dsig != nullptr;
-  if (dir == DIR_FWD) {
-    // only the final F-relaxation writes the sigma' record
-    if (a.mode == SWEEP_FC) launch(k_fwd<Q, SWEEP_FC, false>, grid, NT, 0, st, a);
-    else if (a.mode == SWEEP_FRES) launch(k_fwd<Q, SWEEP_FRES, false>, grid, NT, 0, st, a);
-    else if (rec) launch(k_fwd<Q, SWEEP_CORRF, true>, grid, NT, 0, st, a);
-    else launch(k_fwd<Q, SWEEP_CORRF, false>, grid, NT, 0, st, a);
-  } else if (rec) {
-    if (a.mode == SWEEP_FC) launch(k_adj<Q, SWEEP_FC, true>, grid, NT, 0, st, a);
-    else if (a.mode == SWEEP_FRES) launch(k_adj<Q, SWEEP_FRES, true>, grid, NT, 0, st, a);
-    else launch(k_adj<Q, SWEEP_CORRF, true>, grid, NT, 0, st, a);
-  } else {
-    if (a.mode == SWEEP_FC) launch(k_adj<Q, SWEEP_FC, false>, grid, NT, 0, st, a);
-    else if (a.mode == SWEEP_FRES) launch(k_adj<Q, SWEEP_FRES, false>, grid, NT, 0, st, a);
-    else launch(k_adj<Q, SWEEP_CORRF, false>, grid, NT, 0, st, a);
-  }
+  if (T == 6) sweep_t<Q, 6>(dir, a, grid, st);
+  else if (T == 4) sweep_t<Q, 4>(dir, a, grid, st);
+  else sweep_t<Q, 2>(dir, a, grid, st);
   return hipGetLastError();
 }
 
 template <int Q>
 hipError_t serial(int dir, const SerialArgs& s, hipStream_t st) {
+  constexpr int NT = Geo<Q>::NT;
   SweepArgs a{};
   a.act = s.act;
   a.mode = MODE_SERIAL;
@@ -867,30 +821,31 @@ hipError_t serial(int dir, const SerialArgs& s, hipStream_t st) {
   a.X = s.X;
   a.G = s.G;
   a.dsig = s.dsig;
-  const dim3 grid((s.B + EX * WAVES - 1) / (EX * WAVES), 1);
+  // a layer's 194 kB take a CU about as long to read from L2 as two tiles' products
+  const dim3 grid((s.B + 31) / 32, 1);
   if (dir == DIR_FWD) {
-    if (s.dsig) launch(k_fwd<Q, MODE_SERIAL, true>, grid, NT, 0, st, a);
-    else launch(k_fwd<Q, MODE_SERIAL, false>, grid, NT, 0, st, a);
+    if (s.dsig) launch(k_fwd<Q, MODE_SERIAL, true, 2>, grid, NT, 0, st, a);
+    else launch(k_fwd<Q, MODE_SERIAL, false, 2>, grid, NT, 0, st, a);
   } else {
-    if (s.dsig) launch(k_adj<Q, MODE_SERIAL, true>, grid, NT, 0, st, a);
-    else launch(k_adj<Q, MODE_SERIAL, false>, grid, NT, 0, st, a);
+    if (s.dsig) launch(k_adj<Q, MODE_SERIAL, true, 2>, grid, NT, 0, st, a);
+    else launch(k_adj<Q, MODE_SERIAL, false, 2>, grid, NT, 0, st, a);
   }
   return hipGetLastError();
 }
 
 template <int Q>
 hipError_t resid(int dir, const ResidArgs& a, hipStream_t st, int* partials) {
-  const dim3 grid((unsigned)a.N, (unsigned)((a.B + EX * WAVES - 1) / (EX * WAVES)));
+  const dim3 grid((unsigned)a.N, (unsigned)((a.B + 63) / 64));
   if (partials) *partials = (int)(grid.x * grid.y);
-  if (dir == DIR_FWD) launch(k_resid<Q, DIR_FWD>, grid, NT, 0, st, a);
-  else launch(k_resid<Q, DIR_ADJ>, grid, NT, 0, st, a);
+  if (dir == DIR_FWD) launch(k_resid<Q, DIR_FWD, 4>, grid, Geo<Q>::NT, 0, st, a);
+  else launch(k_resid<Q, DIR_ADJ, 4>, grid, Geo<Q>::NT, 0, st, a);
   return hipGetLastError();
 }
 
 template <int Q>
 hipError_t grad(const GradArgs& a, hipStream_t st) {
-  if (a.dsig) launch(k_grad<Q, true>, dim3(a.N, a.nchunks), NT, 0, st, a);
-  else launch(k_grad<Q, false>, dim3(a.N, a.nchunks), NT, 0, st, a);
+  if (a.dsig) launch(k_grad<Q, true>, dim3(a.N, a.nchunks), Geo<Q>::NT, 0, st, a);
+  else launch(k_grad<Q, false>, dim3(a.N, a.nchunks), Geo<Q>::NT, 0, st, a);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   const size_t tot = (size_t)a.N * (Q * Q + Q);

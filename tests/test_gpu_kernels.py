@@ -197,3 +197,48 @@ def test_narrow_two_tiles_per_wave(dtype, q):
     for part in (slice(0, 33), slice(1000, 1037)):
         us, ls = solve(U[0][part].contiguous(), Lam[N][part].contiguous())
         assert torch.equal(us, u[:, part]) and torch.equal(ls, lam[:, part])
+
+
+# width 220: two, four or six tiles of 16 examples per workgroup by the number of
+# workgroups (six from 512 on, four from 256 on); parts of a batch give the same bits
+@pytest.mark.parametrize("act_name,record", [("smoothrelu", True), ("relu", True), ("tanh", False)])
+def test_wide_tiles_per_workgroup(act_name, record):
+    N, B, q, h = 1024, 200, 220, 0.005
+    _, K, b, U, Lam = dense_problem("f32", q, act_name, N, B, h=h)
+    K = K.clone()  # 16-byte rows, as every fp32 family of width 32 and up needs
+    mg = L.mgrit(cf=4, max_levels=3, max_iter=1)
+
+    def solve(U0, LN):
+        p = L.problem("f32", "dense", act_name, N, U0.shape[0], q, h=h)
+        u, lam = (torch.full((N + 1,) + U0.shape, float("nan"), device="cuda") for _ in range(2))
+        u[0], lam[N] = U0, LN
+        ws, rec = L.alloc_workspace(p, mg), L.alloc_dsig(p) if record else None
+        L.lp_mgrit_forward(p, mg, K, b, u, ws, dsig=rec)
+        L.lp_mgrit_adjoint(p, mg, K, b, u, lam, ws, dsig=rec)
+        return u, lam
+
+    b = b.clone()
+    u, lam = solve(U[0], Lam[N])
+    assert bool(torch.isfinite(u).all()) and bool(torch.isfinite(lam).all())
+    for part in (slice(0, 37), slice(185, 200)):
+        us, ls = solve(U[0][part].contiguous(), Lam[N][part].contiguous())
+        assert torch.equal(us, u[:, part]) and torch.equal(ls, lam[:, part])
+
+
+@pytest.mark.parametrize("B", [1, 31, 65, 129])
+def test_wide_layers(B):
+    N, q, h = 4, 220, 0.05
+    for a in ("tanh", "smoothrelu", "identity"):
+        p, K, b, U, Lam = dense_problem("f32", q, a, N, B)
+        K, b = K.clone(), b.clone()
+        ref = serial_reference(K, b, U, Lam, a, h)
+        for record in (True, False):
+            rec = L.alloc_dsig(p) if record else None
+            dK, db, ws = torch.empty_like(K), torch.empty_like(b), L.alloc_workspace(p)
+            L.lp_serial_forward(p, K, b, U, dsig=rec)
+            L.lp_serial_adjoint(p, K, b, U, Lam, dsig=rec)
+            L.lp_gradient(p, K, b, U, Lam, dK, db, ws, dsig=rec)
+            bound = 16 * N * (q + 8) * EPS["f32"]
+            for got, r, n in ((U, ref[0], 0), (Lam, ref[1], 0), (dK, ref[2], B), (db, ref[3], B)):
+                e = float((got.double() - r).norm() / r.norm())
+                assert e <= bound + 4 * n * EPS["f32"], (a, record, e, bound)
