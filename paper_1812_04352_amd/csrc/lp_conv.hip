@@ -1,5 +1,5 @@
-// 3x3 convolution layers with C = 8 channels (fp32) on the matrix cores
-// (gfx950 v_mfma_f32_16x16x4_f32), as an implicit GEMM.
+// 3x3 convolution layers with C = 8 channels (fp32) on the matrix cores, as an
+// implicit GEMM.
 //
 // Layer operator (Section 2.1, K(theta) a convolution): cross-correlation with
 // zero "same" padding, z[co][y][x] = sum_{ci,ty,tx} K[co][ci][ty][tx] u[ci][y+ty-1][x+tx-1] + b[co].
@@ -8,13 +8,23 @@
 // describe the register and LDS layout). The image is split into
 // "pair-pixels": pair-pixel P = (Y, x) stands for the two output
 // pixels (2Y, x) and (2Y+1, x). A 16 x 16 x 96 product gives the outputs of 16
-// pair-pixels for all (co, dy) in {0..7} x {0,1} (the M = 16 rows), contracting
-// over a 4-row window: k = (ci, r, tx), r = 0..3 the rows 2Y-1 .. 2Y+2. Row dy of
-// the output uses window rows r = dy .. dy+2, so the expanded weight matrix is
-// Wbig[k][(co,dy)] = K[co][ci][r - dy][tx] when 0 <= r - dy <= 2 and 0 otherwise
-// (72 of every 96 products are useful). k-slice s and lane group g = lane/16 map
-// to ci = g + 4 (s / 12), r = (s % 12) / 3, tx = s % 3, so a lane's patch read for
-// slice s is a fixed LDS offset from its pair-pixel's base.
+// pair-pixels for all (co, dy) in {0..7} x {0,1} (the M = 16 rows, row 2 co + dy),
+// contracting over a 4-row window: the 12 window positions (r, tx), r = 0..3 the
+// rows 2Y-1 .. 2Y+2, of 8 channels each. Row dy of the output uses window rows
+// r = dy .. dy+2, so the expanded weight matrix is K[co][ci][r - dy][tx] when
+// 0 <= r - dy <= 2 and 0 otherwise (72 of every 96 products are useful).
+//
+// The sweeps run the product as split bf16 ones (lp_split.h): the contraction is
+// three slices of 32, slice s taking window position 4 s + lane/16 with its 8
+// channels from each lane group, and the image lies in LDS as three bf16 parts with
+// the channels of a pixel together, so a lane reads its operand of a slice and part
+// with one 16-byte read (16 neighbouring pixels per lane group, no conflicts) at a
+// fixed offset from its pair-pixel's base. A lane's accumulators are two
+// neighbouring channels of two pixels: two 4-byte writes per part put them back.
+// A tile takes 18 matrix instructions of 16 cycles and 9 reads, against 24 of 32
+// cycles and 24 reads on v_mfma_f32_16x16x4_f32 with an fp32 image. 28 x 28 images,
+// 256 examples, 256 layers, finest sweeps, us before and now: forward FC 887 / 624,
+// forward FRES 1047 / 778, adjoint FC 880 / 623, adjoint FRES 1099 / 784.
 //
 // The adjoint step applies K^T, a cross-correlation with the kernel flipped and
 // its channel axes swapped; the same product runs with that weight gather.
@@ -24,6 +34,7 @@
 
 #include "lp_device.h"
 #include "lp_internal.h"
+#include "lp_split.h"
 
 namespace lp {
 namespace conv {
@@ -76,25 +87,46 @@ __device__ __forceinline__ void row_copy(float* __restrict__ dst, const float* _
   for (int i = threadIdx.x; i < q; i += nt) dst[i] = src[i];
 }
 
-// Expanded weights of one lane for the 24 k-slices: A-row (co, dy) = (n/2, n%2)
-// with n = lane % 16, slice s and group g = lane / 16. TR selects the adjoint's
-// transposed, flipped kernel.
+// Expanded weights of one lane, split, for the three slices of the sweeps' product:
+// row (co, dy) = (n / 2, n % 2) with n = lane % 16, window position 4 s + lane / 16,
+// the 8 channels, times the layer's sign. TR selects the adjoint's transposed,
+// flipped kernel.
 template <bool TR>
-__device__ __forceinline__ void gather_w(float (&wr)[24], const float* sw, int lane) {
-  const int n = lane & 15, g = lane >> 4;
-  const int co = n >> 1, dy = n & 1;
+__device__ __forceinline__ void gather_w(Split8 (&wr)[3], const float* sw, int lane, float sgn) {
+  const int n = lane & 15, g = lane >> 4, co = n >> 1, dy = n & 1;
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const int q = 4 * s + g, r = q / 3, tx = q - 3 * r, ty = r - dy;
+    const bool in = ty >= 0 && ty <= 2;
+    const int tc = in ? ty : 0;
+    const float* p = sw + (TR ? co * 9 + (2 - tc) * 3 + (2 - tx) : co * 72 + tc * 3 + tx);
+    f32x8 w;
+#pragma unroll
+    for (int ci = 0; ci < CH; ++ci) {
+      const float x = p[ci * (TR ? 72 : 9)];
+      w[ci] = in ? sgn * x : 0.f;
+    }
+    wr[s] = split8(w);
+  }
+}
+
+// The gradient's forward product (without a record) runs on the fp32 instruction
+// from an fp32 image: k-slice s of 24 and lane group g take ci = g + 4 (s / 12),
+// r = (s % 12) / 3, tx = s % 3, the same rows.
+__device__ __forceinline__ void gather_w32(float (&wr)[24], const float* sw, int lane) {
+  const int n = lane & 15, g = lane >> 4, co = n >> 1, dy = n & 1;
 #pragma unroll
   for (int s = 0; s < 24; ++s) {
     const int ci = g + 4 * (s / 12), r = (s % 12) / 3, tx = s % 3, ty = r - dy;
     float w = 0.f;
-    if (ty >= 0 && ty <= 2) w = TR ? sw[ci * 72 + co * 9 + (2 - ty) * 3 + (2 - tx)] : sw[co * 72 + ci * 9 + ty * 3 + tx];
+    if (ty >= 0 && ty <= 2) w = sw[co * 72 + ci * 9 + ty * 3 + tx];
     wr[s] = w;
   }
 }
 
-// acc += Wbig^T-slices x patches of the buffer for one tile
-__device__ __forceinline__ f32x4 conv_tile(const float (&wr)[24], const float* buf, int base, int cs, int pw,
-                                           f32x4 acc) {
+// acc += expanded weights x patches of the fp32 image for one tile
+__device__ __forceinline__ f32x4 conv_tile32(const float (&wr)[24], const float* buf, int base, int cs, int pw,
+                                             f32x4 acc) {
 #pragma unroll
   for (int s = 0; s < 24; ++s) {
     const int off = (s / 12) * 4 * cs + ((s % 12) / 3) * pw + (s % 3);
@@ -106,7 +138,7 @@ __device__ __forceinline__ f32x4 conv_tile(const float (&wr)[24], const float* b
 // ------------------------------------------------------------------ sweeps
 // One workgroup runs one example through one interval (or, serially, through a
 // whole level). The state being evolved lives in registers at the lane's own
-// output pixels; the one LDS image buffer holds whatever the next product reads
+// output pixels; the one LDS image buffer (split, 48 bytes per pixel) holds whatever the next product reads
 // (the forward state, the adjoint's primal state and then s = d * lam), with a
 // zero halo. Wave w owns tiles w*TPW .. w*TPW+TPW-1; a 28 x 28 image (25 tiles)
 // runs on 4 waves, one per SIMD, the last one carrying three ghost tiles (lanes
@@ -119,9 +151,10 @@ __device__ __forceinline__ f32x4 conv_tile(const float (&wr)[24], const float* b
 struct SGeo {
   int H, W;
   int PW;    // padded row length W + 2
-  int CS;    // LDS channel stride: >= (H+2)(W+2) and = 16 (mod 64), so the four
-             // 16-lane groups of a patch read (channels g, g+1, g+2, g+3) hit
-             // disjoint banks
+  int CS;    // channel stride of the gradient's fp32 images: >= (H+2)(W+2) and = 16
+             // (mod 64), so the four 16-lane groups of a patch read (channels g, g+1,
+             // g+2, g+3) hit disjoint banks
+  int PS;    // bytes of one part of the sweeps' split image, 16 per padded pixel
   int HW, q;
   int NPP;   // pair-pixels (H/2) W
   int NT16;  // tiles of 16 pair-pixels
@@ -134,7 +167,7 @@ constexpr int MAXW = 8;  // waves per workgroup at most
 constexpr __host__ __device__ SGeo make_geo(int H, int W) {
   const int phw = (H + 2) * (W + 2);
   const int npp = H / 2 * W, nt16 = (H / 2 * W + 15) / 16;
-  return SGeo{H, W, W + 2, phw + (((16 - phw) % 64) + 64) % 64, H * W, CH * H * W, npp, nt16, (nt16 + TPW - 1) / TPW};
+  return SGeo{H, W, W + 2, phw + (((16 - phw) % 64) + 64) % 64, 16 * phw, H * W, CH * H * W, npp, nt16, (nt16 + TPW - 1) / TPW};
 }
 
 // Geometry of a kernel instance: compile-time for the specialised image sizes
@@ -145,11 +178,13 @@ __device__ __forceinline__ SGeo geo_of(const SGeo& ga) {
   else return make_geo(GH, GW);
 }
 
-// The lane's pair-pixel in tile t: patch origin, own output offsets (register 0:
-// channel 2*(lane/16), row 2Y, column x) and whether it lies in the image; lanes
-// past the last pair-pixel repeat it and never write.
+// The lane's pair-pixel in tile t: patch origin (padded pixel; in the gradient's
+// fp32 image with the lane group's channel), own pixel in the split image (bytes) and
+// in the fp32 image, own output offset (register 0: channel 2*(lane/16), row 2Y,
+// column x) and whether it lies in the image; lanes past the last pair-pixel repeat
+// it and never write.
 struct Px {
-  int base, lds, gl;
+  int base, base32, own, lds, gl;
   bool ok;
 };
 
@@ -159,8 +194,10 @@ __device__ __forceinline__ Px px_of(const SGeo& g, int t, int lane) {
   p.ok = P < g.NPP;
   if (!p.ok) P = g.NPP - 1;
   const int Y = P / g.W, x = P - Y * g.W, grp = lane >> 4;
-  p.base = grp * g.CS + 2 * Y * g.PW + x;
-  p.lds = 2 * grp * g.CS + (2 * Y + 1) * g.PW + x + 1;
+  p.base = 2 * Y * g.PW + x;
+  p.base32 = grp * g.CS + p.base;
+  p.own = 16 * (p.base + g.PW + 1) + 4 * grp;
+  p.lds = 2 * grp * g.CS + p.base + g.PW + 1;
   p.gl = 2 * grp * g.HW + 2 * Y * g.W + x;
   return p;
 }
@@ -181,34 +218,57 @@ __device__ __forceinline__ void st_px(float* __restrict__ dst, f32x4 v, const SG
   for (int r = 0; r < 4; ++r) dst[gl_r(g, p, r)] = v[r];
 }
 
-__device__ __forceinline__ void put_px(float* buf, f32x4 v, const SGeo& g, const Px& p) {
+// own values into the gradient's fp32 image
+__device__ __forceinline__ void put_px32(float* buf, f32x4 v, const SGeo& g, const Px& p) {
 #pragma unroll
   for (int r = 0; r < 4; ++r) buf[lds_r(g, p, r)] = v[r];
 }
 
-// The interior of the zero-halo LDS image (channel stride CS, padded rows PW) to a
-// state row [C][H][W] in global memory: thread i takes values 4i .. 4i+3, which lie
-// in one image row when W % 4 == 0 (else one value at a time).
-__device__ __forceinline__ void store_img(float* __restrict__ dst, const float* buf, const SGeo& g, int nt) {
-  if (g.W % 4 == 0) {
-    for (int i = 4 * (int)threadIdx.x; i < g.q; i += 4 * nt) {
-      const int c = i / g.HW, r = i - c * g.HW, y = r / g.W, x = r - y * g.W;
-      const float* s = buf + c * g.CS + (y + 1) * g.PW + x + 1;
-      *reinterpret_cast<f32x4*>(dst + i) = f32x4{s[0], s[1], s[2], s[3]};
-    }
-  } else {
-    for (int i = threadIdx.x; i < g.q; i += nt) {
-      const int c = i / g.HW, r = i - c * g.HW, y = r / g.W, x = r - y * g.W;
-      dst[i] = buf[c * g.CS + (y + 1) * g.PW + x + 1];
+// own values into the sweeps' split image: per part, two channels of two rows
+__device__ __forceinline__ void put_px(char* buf, f32x4 v, const SGeo& g, const Px& p) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  v = f32x4{v[0], v[2], v[1], v[3]};
+#pragma unroll
+  for (int part = 0; part < 3; ++part) {
+    const u32x2 w = __builtin_bit_cast(u32x2, __builtin_convertvector(v, bf16x4));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      *reinterpret_cast<uint32_t*>(buf + part * g.PS + p.own + 16 * i * g.PW) = w[i];
+      v[2 * i] -= __builtin_bit_cast(float, w[i] << 16);
+      v[2 * i + 1] -= __builtin_bit_cast(float, w[i] & 0xffff0000u);
     }
   }
 }
 
-// Products of the wave's tiles, z[tt] = init + Wbig^T x patches.
-__device__ __forceinline__ void conv_tiles(f32x4 (&z)[TPW], const float (&wr)[24], const float* buf, const SGeo& g,
+// Products of the wave's tiles from the split image, z[tt] = init + weights x
+// patches, the smallest partial products first.
+__device__ __forceinline__ void conv_tiles(f32x4 (&z)[TPW], const Split8 (&wr)[3], const char* buf, const SGeo& g,
                                            int t0, int lane, f32x4 init) {
+  constexpr int ia[6] = {0, 2, 1, 0, 1, 0}, ib[6] = {2, 0, 1, 1, 0, 0};
+  int off[3];
 #pragma unroll
-  for (int tt = 0; tt < TPW; ++tt) z[tt] = conv_tile(wr, buf, px_of(g, t0 + tt, lane).base, g.CS, g.PW, init);
+  for (int s = 0; s < 3; ++s) {
+    const int q = 4 * s + (lane >> 4), r = q / 3;
+    off[s] = 16 * (r * g.PW + q - 3 * r);
+  }
+#pragma unroll
+  for (int tt = 0; tt < TPW; ++tt) {
+    const char* src = buf + 16 * px_of(g, t0 + tt, lane).base;
+    Split8 b[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+      for (int part = 0; part < 3; ++part)
+        b[s].p[part] = *reinterpret_cast<const bf16x8*>(src + off[s] + part * g.PS);
+    f32x4 acc = init;
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+#pragma unroll
+      for (int s = 0; s < 3; ++s)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[s].p[ia[k]], b[s].p[ib[k]], acc, 0, 0, 0);
+    z[tt] = acc;
+  }
 }
 
 __device__ __forceinline__ f32x4 bias_px(const float* sw, int lane) {
@@ -381,23 +441,20 @@ __device__ __forceinline__ Blk sweep_block() {
 // SIMD leave room for it).
 template <int MODE, int GH, int GW, int RK, bool HG>
 __global__ __launch_bounds__(64 * MAXW)
-__attribute__((amdgpu_waves_per_eu(HG || MODE == SWEEP_FRES ? 3 : MODE == SWEEP_CORRF || MODE == MODE_SERIAL ? 4 : 1, 8)))
+__attribute__((amdgpu_waves_per_eu(MODE == SWEEP_CORRF && RK == 1 ? 2 : 3, 8)))
 void k_fwd(SweepArgs a, SGeo ga) {
   constexpr bool REC = RK != 0, RB = RK == 1;
   // weight entries per thread while staging (the specialised geometry fixes the thread count)
   constexpr int WPT = GH ? (WV + 64 * make_geo(GH, GW).NW - 1) / (64 * make_geo(GH, GW).NW) : (WV + 63) / 64;
   const SGeo g = geo_of<GH, GW>(ga);
   extern __shared__ float lds[];
-  float* buf = lds;               // CH * CS
-  float* sw = lds + CH * g.CS;    // two layers
+  char* buf = reinterpret_cast<char*>(lds);  // the split image
+  float* sw = lds + 3 * g.PS / 4;            // two layers
   __shared__ double red[MAXW];
   int lane = threadIdx.x & 63;
-  // the wave's first tile; in the correction sweep it is taken as uniform across
-  // the wave, so the tile bases derived from it live in scalar registers (measured
-  // per mode: 2.8 % faster there, slower or spilling in the others)
-  constexpr bool UNIF = MODE == SWEEP_CORRF;
-  const int wave = threadIdx.x >> 6;
-  const int t0 = (UNIF ? __builtin_amdgcn_readfirstlane(wave) : wave) * TPW, nt = blockDim.x;
+  // the wave's first tile, uniform across the wave, so the tile bases derived from it
+  // live in scalar registers
+  const int t0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) * TPW, nt = blockDim.x;
   const Blk wb = sweep_block();
   const int k = wb.k, Nc = gridDim.x;
   const size_t slice = (size_t)a.B * g.q, eo = (size_t)wb.ex * g.q;
@@ -412,7 +469,7 @@ void k_fwd(SweepArgs a, SGeo ga) {
   const float hl = (float)a.hl, hc = (float)a.hc;
   const long kc = MODE == MODE_SERIAL ? 0 : (long)k * c;
 
-  zero_buf(buf, CH * g.CS, nt);
+  zero_buf(lds, 3 * g.PS / 4, nt);
   stage_w(sw, K, bb, (size_t)kc * a.stride, nt);
   // starting state: C-point k, corrected when a coarse solution is given
   const float* src;
@@ -467,36 +524,33 @@ void k_fwd(SweepArgs a, SGeo ga) {
   // layer; CORRF then also takes the product of the layer before the next C-point
   constexpr bool rec = REC && (MODE == SWEEP_CORRF || MODE == MODE_SERIAL);
   constexpr int extra = MODE == SWEEP_CORRF && rec ? 1 : 0;
-  // FRES on a coarse level parks the coarse step's value Phi_{l+1}(C_k) in its
-  // output row (the next level's right-hand side) instead of holding it in
-  // registers through the interval: with the level's right-hand-side rows also in
-  // flight, holding it spills, and each reload from scratch would wait for those
-  // rows too. The epilogue reads it back together with the upper C-point.
-  constexpr bool PARK = MODE == SWEEP_FRES && HG;
+  // FRES parks the coarse step's value Phi_{l+1}(C_k) in its output row (the next
+  // level's right-hand side) instead of holding it in registers through the
+  // interval, where it spills (and on coarse levels each reload from scratch would
+  // wait for the right-hand-side rows in flight too). The epilogue reads it back
+  // together with the upper C-point.
   float* const gn = MODE == SWEEP_FRES ? static_cast<float*>(a.Gn) + (size_t)(k + 1) * slice + eo : nullptr;
-  f32x4 coarse[PARK ? 1 : TPW];
   for (int j = 0; j < nsteps; ++j) {
     // an empty asm statement makes the lane index opaque to the optimiser, so the
     // tile offsets derived from it are recomputed each step instead of being kept
     // live in registers through the loop (fewer registers, more resident waves)
     asm volatile("" : "+v"(lane));
     const float* swc = sw + (j & 1) * WV;
-    // the serial solve stages in one go (measured faster there)
-    constexpr bool SPLIT = MODE != MODE_SERIAL;
     const size_t nxt = (size_t)(kc + (j + 1 < nsteps ? j + 1 : j + extra)) * a.stride;
-    float wreg[SPLIT ? WPT : 1];
-    if constexpr (SPLIT) stage_fetch<WPT>(wreg, K, bb, nxt, nt);
-    else stage_w(sw + ((j & 1) ^ 1) * WV, K, bb, nxt, nt);
+    float wreg[WPT];
+    stage_fetch<WPT>(wreg, K, bb, nxt, nt);
     f32x4 z[TPW], gv[HG ? TPW : 1];
     if constexpr (HG) {
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) gv[tt] = ld_px(G + (kc + j + 1) * slice + eo, g, px_of(g, t0 + tt, lane));
     }
     {
-      float wr[24];
-      gather_w<false>(wr, swc, lane);
-      const f32x4 bias = bias_px(swc, lane);
-      conv_tiles(z, wr, buf, g, t0, lane, bias);
+      const float sgn = layer_sign((size_t)(kc + j) * a.stride);
+      Split8 wr[3];
+      gather_w<false>(wr, swc, lane, sgn);
+      conv_tiles(z, wr, buf, g, t0, lane, sgn * bias_px(swc, lane));
+#pragma unroll
+      for (int tt = 0; tt < TPW; ++tt) z[tt] *= sgn;
     }
     if constexpr (rec) {
       const size_t blk = (size_t)(kc + j) * a.stride * a.B + wb.ex;
@@ -509,12 +563,8 @@ void k_fwd(SweepArgs a, SGeo ga) {
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
       if (MODE == SWEEP_FRES && j == 0) {
-        if constexpr (PARK) {
-          const Px p = px_of(g, t0 + tt, lane);
-          if (p.ok) st_px(gn, v[tt] + hc * z[tt], g, p);
-        } else {
-          coarse[tt] = v[tt] + hc * z[tt];
-        }
+        const Px p = px_of(g, t0 + tt, lane);
+        if (p.ok) st_px(gn, v[tt] + hc * z[tt], g, p);
       }
       v[tt] = v[tt] + hl * z[tt];
       if constexpr (HG) v[tt] += gv[tt];
@@ -524,14 +574,13 @@ void k_fwd(SweepArgs a, SGeo ga) {
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
       const Px p = px_of(g, t0 + tt, lane);
-      if (p.ok) put_px(buf, v[tt], g, p);
+      if (p.ok) {
+        put_px(buf, v[tt], g, p);
+        if (MODE == SWEEP_CORRF || MODE == MODE_SERIAL) st_px(X + (kc + j + 1) * slice + eo, v[tt], g, p);
+      }
     }
-    if constexpr (SPLIT) stage_put<WPT>(sw + ((j & 1) ^ 1) * WV, wreg, nt);
+    stage_put<WPT>(sw + ((j & 1) ^ 1) * WV, wreg, nt);
     __syncthreads();
-    // the new state is written out from the LDS image in row order, four values
-    // per thread and store (the next write of the buffer is a step away, behind
-    // that step's first barrier)
-    if (MODE == SWEEP_CORRF || MODE == MODE_SERIAL) store_img(X + (kc + j + 1) * slice + eo, buf, g, nt);
   }
 
   if constexpr (extra != 0) {
@@ -539,9 +588,12 @@ void k_fwd(SweepArgs a, SGeo ga) {
     // buffer) and that layer's weights (staged by the last step)
     const float* swc = sw + (nsteps & 1) * WV;
     f32x4 z[TPW];
-    float wr[24];
-    gather_w<false>(wr, swc, lane);
-    conv_tiles(z, wr, buf, g, t0, lane, bias_px(swc, lane));
+    const float sgn = layer_sign((size_t)(kc + nsteps) * a.stride);
+    Split8 wr[3];
+    gather_w<false>(wr, swc, lane, sgn);
+    conv_tiles(z, wr, buf, g, t0, lane, sgn * bias_px(swc, lane));
+#pragma unroll
+    for (int tt = 0; tt < TPW; ++tt) z[tt] *= sgn;
     const size_t blk = (size_t)(kc + nsteps) * a.stride * a.B + wb.ex;
     rec_put<RB>(a.dsig, blk, g, t0, lane, z, a.act);
   }
@@ -555,35 +607,22 @@ void k_fwd(SweepArgs a, SGeo ga) {
   } else if (MODE == SWEEP_FRES) {
     const float* cn = Cs + (size_t)(k + 1) * a.cs_stride * slice + eo;
     double acc = 0.0;
-    if constexpr (PARK) {
-      asm volatile("" ::: "memory");  // read the parked row back from memory
-      f32x4 cv[TPW], pk[TPW];
+    asm volatile("" ::: "memory");  // read the parked row back from memory
+    f32x4 cv[TPW], pk[TPW];
 #pragma unroll
-      for (int tt = 0; tt < TPW; ++tt) {
-        const Px p = px_of(g, t0 + tt, lane);
-        cv[tt] = ld_px(cn, g, p);
-        pk[tt] = ld_px(gn, g, p);  // this lane's own step-0 stores (ghost lanes: unused)
-      }
+    for (int tt = 0; tt < TPW; ++tt) {
+      const Px p = px_of(g, t0 + tt, lane);
+      cv[tt] = ld_px(cn, g, p);
+      pk[tt] = ld_px(gn, g, p);  // this lane's own step-0 stores (ghost lanes: unused)
+    }
 #pragma unroll
-      for (int tt = 0; tt < TPW; ++tt) {
-        const Px p = px_of(g, t0 + tt, lane);
-        if (p.ok) {
-          const f32x4 rr = v[tt] - cv[tt];
+    for (int tt = 0; tt < TPW; ++tt) {
+      const Px p = px_of(g, t0 + tt, lane);
+      if (p.ok) {
+        const f32x4 rr = v[tt] - cv[tt];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) acc += (double)rr[r] * (double)rr[r];
-          st_px(gn, v[tt] - pk[tt], g, p);  // g_{l+1}^{k+1} = f_{k+1} - Phi_{l+1}(C_k)
-        }
-      }
-    } else {
-#pragma unroll
-      for (int tt = 0; tt < TPW; ++tt) {
-        const Px p = px_of(g, t0 + tt, lane);
-        if (p.ok) {
-          const f32x4 rr = v[tt] - ld_px(cn, g, p);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc += (double)rr[r] * (double)rr[r];
-          st_px(gn, v[tt] - coarse[tt], g, p);  // g_{l+1}^{k+1} = f_{k+1} - Phi_{l+1}(C_k)
-        }
+        for (int r = 0; r < 4; ++r) acc += (double)rr[r] * (double)rr[r];
+        st_px(gn, v[tt] - pk[tt], g, p);  // g_{l+1}^{k+1} = f_{k+1} - Phi_{l+1}(C_k)
       }
     }
     if (a.xn_every > 0 && (k + 1) % a.xn_every == 0)
@@ -608,22 +647,21 @@ void k_fwd(SweepArgs a, SGeo ga) {
 // lam' = lam + h K^T s (+ g).
 template <int MODE, int GH, int GW, int RK, bool HG>
 __global__ __launch_bounds__(64 * MAXW)
-__attribute__((amdgpu_waves_per_eu(HG ? 3 : RK == 1 ? 4 : RK == 2 ? 3 : 1, 8)))
+__attribute__((amdgpu_waves_per_eu(RK == 0 || (RK == 2 && (MODE == SWEEP_CORRF || MODE == MODE_SERIAL)) ? 2 : 3, 8)))
 void k_adj(SweepArgs a, SGeo ga) {
   constexpr bool REC = RK != 0, RB = RK == 1;
   // weight entries per thread while staging (the specialised geometry fixes the thread count)
   constexpr int WPT = GH ? (WV + 64 * make_geo(GH, GW).NW - 1) / (64 * make_geo(GH, GW).NW) : (WV + 63) / 64;
   const SGeo g = geo_of<GH, GW>(ga);
   extern __shared__ float lds[];
-  float* buf = lds;               // CH * CS: u, then s
-  float* sw = lds + CH * g.CS;    // two layers
+  char* buf = reinterpret_cast<char*>(lds);  // the split image: u, then s
+  float* sw = lds + 3 * g.PS / 4;            // two layers
   __shared__ double red[MAXW];
   int lane = threadIdx.x & 63;
-  // the wave's first tile; in the FRES sweep with a record it is taken as uniform
-  // across the wave, so the tile bases derived from it live in scalar registers
-  // (this removes the finest FRES kernel's spill; measured per mode, the other
-  // sweeps are slower or spill with it)
-  constexpr bool UNIF = MODE == SWEEP_FRES && RK != 0;
+  // the wave's first tile; with a record the FC and FRES sweeps take it as uniform
+  // across the wave, so the tile bases derived from it live in scalar registers (which
+  // removes their spills; the other sweeps spill with it)
+  constexpr bool UNIF = (MODE == SWEEP_FRES || MODE == SWEEP_FC) && RK != 0;
   const int wave = threadIdx.x >> 6;
   const int t0 = (UNIF ? __builtin_amdgcn_readfirstlane(wave) : wave) * TPW, nt = blockDim.x;
   const Blk wb = sweep_block();
@@ -642,7 +680,7 @@ void k_adj(SweepArgs a, SGeo ga) {
   const long top = MODE == MODE_SERIAL ? (long)a.Nl : (long)(k + 1) * c;
   const size_t ustep = (size_t)a.stride * slice;
 
-  zero_buf(buf, CH * g.CS, nt);
+  zero_buf(lds, 3 * g.PS / 4, nt);
   stage_w(sw, K, bb, (size_t)(top - 1) * a.stride, nt);
   const float* src;
   const float* vsrc = nullptr;
@@ -696,10 +734,12 @@ void k_adj(SweepArgs a, SGeo ga) {
     constexpr bool OPAQUE = REC ? (MODE == SWEEP_FC || MODE == SWEEP_FRES) : MODE != SWEEP_FRES;
     if constexpr (OPAQUE) asm volatile("" : "+v"(lane));
     const long i = top - 1 - j;
+    const float sgn = layer_sign((size_t)i * a.stride);
     const bool more = j + 1 < nsteps;
     const float* swc = sw + (j & 1) * WV;
-    // the correction and serial sweeps stage in one go: their registers are spoken for
-    constexpr bool SPLIT = MODE == SWEEP_FC || MODE == SWEEP_FRES;
+    // the coarse correction and serial sweeps with ReLU's bits stage in one go: their
+    // registers are spoken for
+    constexpr bool SPLIT = !(RK == 1 && HG && (MODE == SWEEP_CORRF || MODE == MODE_SERIAL));
     float wreg[SPLIT ? WPT : 1];
     if constexpr (SPLIT) stage_fetch<WPT>(wreg, K, bb, (size_t)(more ? i - 1 : i) * a.stride, nt);
     else stage_w(sw + ((j & 1) ^ 1) * WV, K, bb, (size_t)(more ? i - 1 : i) * a.stride, nt);
@@ -709,14 +749,15 @@ void k_adj(SweepArgs a, SGeo ga) {
       for (int tt = 0; tt < TPW; ++tt) dd[tt] = rec_val<RB>(rn, tt);
       if (more) rn = rec_load<RB>(a.dsig, (size_t)(i - 1) * a.stride * a.B + wb.ex, g, t0, lane);
     } else {
-      float wr[24];
-      gather_w<false>(wr, swc, lane);
-      const f32x4 bias = bias_px(swc, lane);
-      conv_tiles(dd, wr, buf, g, t0, lane, bias);
+      Split8 wr[3];
+      gather_w<false>(wr, swc, lane, sgn);
+      conv_tiles(dd, wr, buf, g, t0, lane, sgn * bias_px(swc, lane));
+#pragma unroll
+      for (int tt = 0; tt < TPW; ++tt) dd[tt] *= sgn;
       act_tiles<true>(dd, a.act);
     }
-    float wt[24];
-    gather_w<true>(wt, swc, lane);
+    Split8 wt[3];
+    gather_w<true>(wt, swc, lane, sgn);
     // every read of u is done (with the record, the buffer was last read by the
     // previous step's transposed product, which ended with a barrier)
     if (!REC) __syncthreads();
@@ -742,7 +783,7 @@ void k_adj(SweepArgs a, SGeo ga) {
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
       const Px p = px_of(g, t0 + tt, lane);
-      lam[tt] = lam[tt] + hl * w[tt];
+      lam[tt] = lam[tt] + (sgn * hl) * w[tt];
       if constexpr (HG) lam[tt] += gv[tt];
       else if (gi) lam[tt] += ld_px(gi, g, p);
       if (xo && p.ok) st_px(xo, lam[tt], g, p);
@@ -795,13 +836,14 @@ void k_adj(SweepArgs a, SGeo ga) {
         for (int r = 0; r < 4; ++r) acc += (double)rr[r] * (double)rr[r];
       }
     }
-    float wt[24];
-    gather_w<true>(wt, sw, lane);
+    const float sgn = layer_sign((size_t)(top - nsteps) * a.stride);
+    Split8 wt[3];
+    gather_w<true>(wt, sw, lane, sgn);
     __syncthreads();
     f32x4 w[TPW];
     conv_tiles(w, wt, buf, g, t0, lane, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-    for (int tt = 0; tt < TPW; ++tt) cu[tt] += hc * w[tt];
+    for (int tt = 0; tt < TPW; ++tt) cu[tt] += (sgn * hc) * w[tt];
     float* gn = static_cast<float*>(a.Gn) + (size_t)k * slice + eo;
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
@@ -830,8 +872,8 @@ void k_adj(SweepArgs a, SGeo ga) {
 template <int DIR>
 __global__ __launch_bounds__(64 * MAXW) void k_resid(ResidArgs a, SGeo g) {
   extern __shared__ float lds[];
-  float* buf = lds;              // CH * CS: U[n], then (adjoint) s
-  float* sw = lds + CH * g.CS;   // the layer's weights
+  char* buf = reinterpret_cast<char*>(lds);  // the split image: U[n], then (adjoint) s
+  float* sw = lds + 3 * g.PS / 4;            // the layer's weights
   __shared__ double red[MAXW];
   const int lane = threadIdx.x & 63, t0 = (threadIdx.x >> 6) * TPW, nt = blockDim.x;
   const int n = blockIdx.x;
@@ -839,7 +881,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resid(ResidArgs a, SGeo g) {
   const float* U = static_cast<const float*>(a.U);
   const float* Lm = static_cast<const float*>(a.Lam);
   const float h = (float)a.h;
-  zero_buf(buf, CH * g.CS, nt);
+  zero_buf(lds, 3 * g.PS / 4, nt);
   stage_w(sw, static_cast<const float*>(a.K), static_cast<const float*>(a.b), n, nt);
   f32x4 un[TPW];
 #pragma unroll
@@ -851,11 +893,14 @@ __global__ __launch_bounds__(64 * MAXW) void k_resid(ResidArgs a, SGeo g) {
     if (p.ok) put_px(buf, un[tt], g, p);
   }
   __syncthreads();
+  const float sgn = layer_sign(n);
   f32x4 z[TPW];
   {
-    float wr[24];
-    gather_w<false>(wr, sw, lane);
-    conv_tiles(z, wr, buf, g, t0, lane, bias_px(sw, lane));
+    Split8 wr[3];
+    gather_w<false>(wr, sw, lane, sgn);
+    conv_tiles(z, wr, buf, g, t0, lane, sgn * bias_px(sw, lane));
+#pragma unroll
+    for (int tt = 0; tt < TPW; ++tt) z[tt] *= sgn;
   }
   double acc = 0.0;
   if (DIR == DIR_FWD) {
@@ -880,15 +925,15 @@ __global__ __launch_bounds__(64 * MAXW) void k_resid(ResidArgs a, SGeo g) {
       if (p.ok) put_px(buf, z[tt] * lam[tt], g, p);
     }
     __syncthreads();
-    float wt[24];
-    gather_w<true>(wt, sw, lane);
+    Split8 wt[3];
+    gather_w<true>(wt, sw, lane, sgn);
     f32x4 w[TPW];
     conv_tiles(w, wt, buf, g, t0, lane, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
       const Px p = px_of(g, t0 + tt, lane);
       if (!p.ok) continue;
-      const f32x4 rr = (lam[tt] + h * w[tt]) - ld_px(Lm + (size_t)n * slice + eo, g, p);
+      const f32x4 rr = (lam[tt] + (sgn * h) * w[tt]) - ld_px(Lm + (size_t)n * slice + eo, g, p);
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc += (double)rr[r] * (double)rr[r];
     }
@@ -955,7 +1000,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
   }
   __syncthreads();  // buffers zeroed, weights staged
   float wf[24];
-  gather_w<false>(wf, sw, lane);
+  gather_w32(wf, sw, lane);
   const f32x4 bias = bias_px(sw, lane);
   // s = sigma' * lam at the lane's own pixels into the s image, and into db
   auto put_s = [&](const f32x4 (&z)[TPW]) {
@@ -964,7 +1009,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
       const Px p = px_of(g, t0 + tt, lane);
       if (p.ok) {
         const f32x4 s = z[tt] * lam[tt];
-        put_px(bs, s, g, p);
+        put_px32(bs, s, g, p);
         db0 += s[0] + s[1];
         db1 += s[2] + s[3];
       }
@@ -996,7 +1041,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
       const Px p = px_of(g, t0 + tt, lane);
-      if (p.ok) put_px(bu, un[tt], g, p);
+      if (p.ok) put_px32(bu, un[tt], g, p);
     }
     if constexpr (REC) put_rec_s();
   }
@@ -1007,7 +1052,9 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
       f32x4 z[TPW];
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) lam[tt] = ld_px(Lm + (size_t)e * g.q, g, px_of(g, t0 + tt, lane));
-      conv_tiles(z, wf, bu, g, t0, lane, bias);
+#pragma unroll
+      for (int tt = 0; tt < TPW; ++tt)
+        z[tt] = conv_tile32(wf, bu, px_of(g, t0 + tt, lane).base32, g.CS, g.PW, bias);
       act_tiles<true>(z, a.act);
       put_s(z);
       __syncthreads();
@@ -1045,7 +1092,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) {
         const Px p = px_of(g, t0 + tt, lane);
-        if (p.ok) put_px(bu, un[tt], g, p);
+        if (p.ok) put_px32(bu, un[tt], g, p);
       }
       if constexpr (REC) put_rec_s();
     }
@@ -1111,7 +1158,7 @@ namespace {
 
 conv::SGeo sweep_geo(const Shape& s) { return conv::make_geo(s.H, s.W); }
 
-size_t sweep_lds(const conv::SGeo& g) { return (size_t)(conv::CH * g.CS + 2 * conv::WV) * sizeof(float); }
+size_t sweep_lds(const conv::SGeo& g) { return (size_t)3 * g.PS + 2 * conv::WV * sizeof(float); }
 
 // Sweep kernels with the geometry as template arguments (0, 0: runtime).
 // Only the forward CORRF and serial kernels write the record; every adjoint

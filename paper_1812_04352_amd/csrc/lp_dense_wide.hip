@@ -163,6 +163,14 @@ __device__ __forceinline__ void apply(Val<T>& z, int act, bool ok1) {
     if (!ok1) z[t][1] = 0.f;
 }
 
+template <int T>
+__device__ __forceinline__ void scale(Val<T>& z, float f) {
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int m = 0; m < 2; ++m) z[t][m] *= f;
+}
+
 // v = c + (v' - c) (Algorithm 1, the coarse-grid correction of a C-point)
 template <int Q, int T>
 __device__ __forceinline__ void correct(Val<T>& v, const float* cs, const float* vs, const Ctx<Q, T>& c) {
@@ -231,18 +239,19 @@ __device__ __forceinline__ void fetch_a(Raw& a, const float* __restrict__ Kn, in
   }
 }
 
-// Publishes the wave's values: split, panel w of every tile.
+// Publishes the wave's values times the sign of the layer that will use them: split,
+// panel w of every tile.
 template <int Q, int T>
-__device__ __forceinline__ void publish(bf16x8* sh, const Val<T>& v, const Ctx<Q, T>& c) {
+__device__ __forceinline__ void publish(bf16x8* sh, const Val<T>& v, const Ctx<Q, T>& c, float sgn) {
 #pragma unroll
   for (int t = 0; t < T; ++t) {
-    const Split8 f = split8(v[t][0], v[t][1]);
+    const Split8 f = split8(sgn * v[t][0], sgn * v[t][1]);
 #pragma unroll
     for (int part = 0; part < 3; ++part) sh[((t * Geo<Q>::NP + c.w) * 3 + part) * 64 + c.lane] = f.p[part];
   }
 }
 
-// z += K_n v (or K_n^T v) for the published v. Two panels of weights are in flight;
+// z += K_n v (or K_n^T v) for the published v (sign included). Two panels of weights are in flight;
 // q0, q1 hold panels 0 and 1 on entry and those of the next product (Knext, kind
 // NTR; nullptr: none) on return.
 template <int Q, int T, bool TR, bool NTR>
@@ -327,7 +336,8 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
     correct<Q, T>(v, Cs + (size_t)k * a.cs_stride * slice, Vn + (size_t)k * slice, cx);
     if (k > 0) store_rows<Q, T>(X + kc * slice, v, cx);
   }
-  publish<Q, T>(sh, v, cx);
+  auto sign = [&](int j) { return layer_sign((size_t)(kc + j) * a.stride); };
+  publish<Q, T>(sh, v, cx, sign(0));
   __syncthreads();
   // FRES parks the coarse step's value v + h_c sigma(z) of the first layer in its
   // Gn row and finishes g_{l+1}^{k+1} = v - (that value) after the interval, so it
@@ -335,14 +345,16 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
   float* gn = MODE == SWEEP_FRES ? static_cast<float*>(a.Gn) + (size_t)(k + 1) * slice : nullptr;
   auto product = [&](Val<T>& z, int j) {
     const float* bn = bb + (size_t)(kc + j) * a.stride * Q;
+    const float sgn = sign(j);
     f32x4 b2[2];
     load2(b2, bn, cx.ok1);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-      z[t][0] = b2[0];
-      z[t][1] = b2[1];
+      z[t][0] = sgn * b2[0];
+      z[t][1] = sgn * b2[1];
     }
     prod<Q, T, false, false>(z, layer(j), sh, cx, q0, q1, j + 1 < nsteps + (extra ? 1 : 0) ? layer(j + 1) : nullptr);
+    scale<T>(z, sgn);
   };
   for (int j = 0; j < nsteps; ++j) {
     Val<T> z;
@@ -377,7 +389,7 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
     if (MODE == SWEEP_CORRF || MODE == MODE_SERIAL) store_rows<Q, T>(X + (kc + j + 1) * slice, v, cx);
     if (j + 1 < nsteps || extra) {
       __syncthreads();  // every read of the old state is done
-      publish<Q, T>(sh, v, cx);
+      publish<Q, T>(sh, v, cx, sign(j + 1));
       __syncthreads();
     }
   }
@@ -424,13 +436,14 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
   }
 }
 
-// s = sigma'(K_n u^n + b_n) * v of the fine state n, published: sigma' from the
+// s = sigma'(K_n u^n + b_n) * v of the fine state n, published (times the layer's sign): sigma' from the
 // record, or by the forward product (whose weights q0, q1 hold on entry; on return
 // they hold the transposed product's). Holds barriers; the caller's reads of sh are
 // done.
 template <int Q, bool REC, int T>
 __device__ __forceinline__ void publish_s(const Val<T>& v, const SweepArgs& a, size_t n, size_t slice, bf16x8* sh,
                                           const Ctx<Q, T>& cx, Raw& q0, Raw& q1) {
+  const float sgn = layer_sign(n);
   Val<T> d;
   if constexpr (REC) {
 #pragma unroll
@@ -438,16 +451,17 @@ __device__ __forceinline__ void publish_s(const Val<T>& v, const SweepArgs& a, s
   } else {
     const float* Kn = static_cast<const float*>(a.K) + n * (Q * Q);
     load_rows<Q, T>(d, static_cast<const float*>(a.Uf) + n * slice, cx);
-    publish<Q, T>(sh, d, cx);
+    publish<Q, T>(sh, d, cx, sgn);
     __syncthreads();
     f32x4 b2[2];
     load2(b2, static_cast<const float*>(a.b) + n * Q + 32 * cx.w + 4 * cx.g, cx.ok1);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-      d[t][0] = b2[0];
-      d[t][1] = b2[1];
+      d[t][0] = sgn * b2[0];
+      d[t][1] = sgn * b2[1];
     }
     prod<Q, T, false, true>(d, Kn, sh, cx, q0, q1, Kn);
+    scale<T>(d, sgn);
     apply<true, T>(d, a.act, cx.ok1);
     __syncthreads();
   }
@@ -455,7 +469,7 @@ __device__ __forceinline__ void publish_s(const Val<T>& v, const SweepArgs& a, s
   for (int t = 0; t < T; ++t)
 #pragma unroll
     for (int m = 0; m < 2; ++m) d[t][m] = d[t][m] * v[t][m];
-  publish<Q, T>(sh, d, cx);
+  publish<Q, T>(sh, d, cx, sgn);
   __syncthreads();
 }
 
@@ -514,7 +528,7 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
     for (int t = 0; t < T; ++t) {
       if (!cx.ok1) w[t][1] = 0.f;
 #pragma unroll
-      for (int m = 0; m < 2; ++m) v[t][m] = v[t][m] + hl * w[t][m];
+      for (int m = 0; m < 2; ++m) v[t][m] = v[t][m] + (layer_sign(n) * hl) * w[t][m];
       if (Gr) {
         f32x4 gv[2];
         load2(gv, Gr + (size_t)i * slice + cx.row[t], cx.ok1);
@@ -566,7 +580,7 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
       f32x4 x[2];
       load2(x, gn + cx.row[t], cx.ok1);
 #pragma unroll
-      for (int m = 0; m < 2; ++m) x[m] = x[m] - (v[t][m] + hc * w[t][m]);  // g_{l+1}^k
+      for (int m = 0; m < 2; ++m) x[m] = x[m] - (v[t][m] + (layer_sign(n) * hc) * w[t][m]);  // g_{l+1}^k
       store2(gn + cx.row[t], x, cx.ok1);
     }
   }
@@ -607,16 +621,18 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
   fetch_a<Q, false>(q1, Kn, 1, cx.w, cx.lane);
   Val<T> v, z;
   load_rows<Q, T>(v, U + (size_t)n * slice, cx);
-  publish<Q, T>(sh, v, cx);
+  const float sgn = layer_sign(n);
+  publish<Q, T>(sh, v, cx, sgn);
   __syncthreads();
   f32x4 b2[2];
   load2(b2, static_cast<const float*>(a.b) + (size_t)n * Q + 32 * cx.w + 4 * cx.g, cx.ok1);
 #pragma unroll
   for (int t = 0; t < T; ++t) {
-    z[t][0] = b2[0];
-    z[t][1] = b2[1];
+    z[t][0] = sgn * b2[0];
+    z[t][1] = sgn * b2[1];
   }
   prod<Q, T, false, true>(z, Kn, sh, cx, q0, q1, DIR == DIR_ADJ ? Kn : nullptr);
+  scale<T>(z, sgn);
   const float* next = DIR == DIR_FWD ? U + (size_t)(n + 1) * slice : L + (size_t)n * slice;
   if constexpr (DIR == DIR_FWD) {
     apply<false, T>(z, a.act, cx.ok1);
@@ -628,7 +644,7 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
       for (int m = 0; m < 2; ++m) z[t][m] = z[t][m] * v[t][m];
     __syncthreads();
-    publish<Q, T>(sh, z, cx);
+    publish<Q, T>(sh, z, cx, sgn);
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < T; ++t) z[t][0] = z[t][1] = 0.f;
@@ -636,6 +652,7 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
     for (int t = 0; t < T; ++t)
       if (!cx.ok1) z[t][1] = 0.f;
+    scale<T>(z, sgn);
   }
   double acc = 0.0;
 #pragma unroll
@@ -692,16 +709,18 @@ __global__ __launch_bounds__(Geo<Q>::NT) void k_grad(GradArgs a) {
       Raw q0, q1;
       fetch_a<Q, false>(q0, Kn, 0, cx.w, cx.lane);
       fetch_a<Q, false>(q1, Kn, 1, cx.w, cx.lane);
-      publish<Q, GT>(sh, u, cx);
+      const float sgn = layer_sign(n);
+      publish<Q, GT>(sh, u, cx, sgn);
       __syncthreads();
       f32x4 b2[2];
       load2(b2, static_cast<const float*>(a.b) + (size_t)n * Q + 32 * cx.w + 4 * cx.g, cx.ok1);
 #pragma unroll
       for (int t = 0; t < GT; ++t) {
-        s[t][0] = b2[0];
-        s[t][1] = b2[1];
+        s[t][0] = sgn * b2[0];
+        s[t][1] = sgn * b2[1];
       }
       prod<Q, GT, false, false>(s, Kn, sh, cx, q0, q1, nullptr);
+      scale<GT>(s, sgn);
       apply<true, GT>(s, a.act, cx.ok1);
     }
 #pragma unroll

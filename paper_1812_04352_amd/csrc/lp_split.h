@@ -11,6 +11,16 @@
 // instruction (one bf16 instruction sums 32 terms at once, the fp32 chain rounds
 // every fourth). The split needs no scaling (bf16 has fp32's exponent range); an
 // infinite or NaN value gives NaN.
+//
+// The accumulation rounds towards minus infinity by a small part of its last place
+// (the mean error of sums of positive terms is -0.8e-9, -3.5e-9 and -7.7e-9 for 32, 96
+// and 224 terms; the fp32 instruction has none), which adds up over layers, pixels
+// and examples in sums that nearly cancel. So a product is formed with the sign of
+// its layer, layer_sign(n) K_n v, and the sign is taken back afterwards: the errors
+// of the layers then cancel instead (the bias gradients of 64 convolution layers of
+// 500 images: error 7e-7 to 2.2e-6 without the sign, 2e-7 to 6e-7 with it and
+// with the fp32 instruction). The sign depends on the fine layer index alone, so that
+// every level and every kernel evaluates a layer the same way bit for bit.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -21,6 +31,12 @@ namespace lp {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float split_f32x4 __attribute__((ext_vector_type(4)));
+
+// -1 for layers with an odd number of one bits, which alternates evenly on the
+// layers n = 0, c^l, 2 c^l, .. of every level l too
+__device__ __forceinline__ float layer_sign(size_t n) {
+  return __builtin_popcountll((unsigned long long)n) & 1 ? -1.f : 1.f;
+}
 
 // Eight values of a lane, split.
 struct Split8 {

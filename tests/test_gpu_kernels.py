@@ -242,3 +242,36 @@ def test_wide_layers(B):
             for got, r, n in ((U, ref[0], 0), (Lam, ref[1], 0), (dK, ref[2], B), (db, ref[3], B)):
                 e = float((got.double() - r).norm() / r.norm())
                 assert e <= bound + 4 * n * EPS["f32"], (a, record, e, bound)
+
+
+# convolution sweeps read their products from a split image in LDS: odd widths, the
+# narrowest and the largest images, ghost lanes in the last tile
+@pytest.mark.parametrize("H,W", [(2, 1), (4, 9), (12, 13), (28, 28), (30, 28)])
+def test_conv_layers(H, W):
+    N, B, h = 4, 3, 0.1
+    for a in ("tanh", "smoothrelu", "identity"):
+        p = L.problem("f32", "conv3x3", a, N, B, 8, H, W, h=h)
+        K, b = rnd(1, N, 8, 8, 3, 3, std=0.15), rnd(2, N, 8, std=0.1)
+        U, Lam = (torch.full((N + 1, B, 8, H, W), float("nan"), device="cuda") for _ in range(2))
+        U[0], Lam[N] = rnd(3, B, 8, H, W), rnd(4, B, 8, H, W)
+        Kd, bd = K.double().cpu(), b.double().cpu()[:, None, :, None, None]
+        u = [U[0].double().cpu()]
+        for n in range(N):
+            u.append(u[-1] + h * act(torch.conv2d(u[-1], Kd[n], padding=1) + bd[n], a))
+        lam, dK = [Lam[N].double().cpu()], []
+        for n in reversed(range(N)):
+            s = dact(torch.conv2d(u[n], Kd[n], padding=1) + bd[n], a) * lam[0]
+            dK.insert(0, h * torch.nn.grad.conv2d_weight(u[n], Kd[n].shape, s, padding=1))
+            lam.insert(0, lam[0] + h * torch.nn.grad.conv2d_input(s.shape, Kd[n], s, padding=1))
+        u, lam, dK = torch.stack(u), torch.stack(lam), torch.stack(dK)
+        for record in (True, False):
+            rec = L.alloc_dsig(p) if record else None
+            gK, gb, ws = torch.empty_like(K), torch.empty_like(b), L.alloc_workspace(p)
+            L.lp_serial_forward(p, K, b, U, dsig=rec)
+            L.lp_serial_adjoint(p, K, b, U, Lam, dsig=rec)
+            L.lp_gradient(p, K, b, U, Lam, gK, gb, ws, dsig=rec)
+            # 72-term products over N layers (growth below 16), then sums over the pixels
+            bound = 16 * N * (72 + 8) * EPS["f32"]
+            for got, r, n in ((U, u, 0), (Lam, lam, 0), (gK, dK, B * H * W)):
+                e = float((got.double().cpu() - r).norm() / r.norm())
+                assert e <= bound + 4 * n * EPS["f32"], (a, record, e, bound)
