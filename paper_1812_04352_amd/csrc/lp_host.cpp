@@ -579,6 +579,7 @@ hipError_t launch_serial(const Shape& s, int dir, const SerialArgs& a, hipStream
 hipError_t launch_resid(const Shape& s, int dir, const ResidArgs& a, hipStream_t st, int* partials) {
   if (s.layer != 0) return conv_resid(s, dir, a, st, partials);
   if (use_wide(s)) return wide_resid(s.C, dir, a, st, partials);
+  if (use_mfma(s)) return mfma_resid(s.C, dir, a, st, partials);
   if (narrow_supported(s.dtype, s.C)) return narrow_resid(s.dtype, s.C, dir, a, st, partials);
   return dense_resid_f32(s.C, dir, a, st, partials);
 }

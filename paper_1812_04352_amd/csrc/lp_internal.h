@@ -157,6 +157,7 @@ hipError_t narrow_grad(int dtype, int q, const GradArgs& a, hipStream_t st);
 bool mfma_width_supported(int q);
 hipError_t mfma_sweep(int q, int dir, const SweepArgs& a, hipStream_t st, int* partials);
 hipError_t mfma_serial(int q, int dir, const SerialArgs& a, hipStream_t st);
+hipError_t mfma_resid(int q, int dir, const ResidArgs& a, hipStream_t st, int* partials);
 hipError_t mfma_grad(int q, const GradArgs& a, hipStream_t st);
 int dense_grad_chunks(int B, int N);
 // C-point storage (c = 4): forward F-relaxation of intervals k0 .. k0 + nk - 1 from the

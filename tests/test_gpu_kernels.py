@@ -275,3 +275,27 @@ def test_conv_layers(H, W):
             for got, r, n in ((U, u, 0), (Lam, lam, 0), (gK, dK, B * H * W)):
                 e = float((got.double().cpu() - r).norm() / r.norm())
                 assert e <= bound + 4 * n * EPS["f32"], (a, record, e, bound)
+
+
+# Residual norms on the matrix cores: a wave takes 16 examples, a workgroup 64 through a
+# run of 1 to 8 layers (by ntiles N / 4096), the last run being shorter. Against the
+# definition in 64 bits: an entry's error is at most (q + 8) u of its terms, which the
+# states bound (h |K| < 1 here), so (q + 8) u (|V| + |M|) bounds the norm's.
+@pytest.mark.parametrize("q", [32, 64])
+@pytest.mark.parametrize("N,B", [(3, 1), (6, 17), (5, 64), (130, 129), (1027, 700), (1027, 2047)])
+def test_dense_residual_runs(q, N, B):
+    for a in ("tanh", "smoothrelu", "identity"):
+        p, K, b, _, _ = dense_problem("f32", q, a, N, B, h=0.05)
+        V, M = rnd(7, N + 1, B, q, dtype=torch.float32), rnd(8, N + 1, B, q, dtype=torch.float32)
+        ws = L.alloc_workspace(p)
+        rs = ra = 0.0
+        for n in range(N):
+            u, k = V[n].double(), K[n].double()
+            z = u @ k.T.contiguous() + b[n].double()
+            rs += float((u + 0.05 * act(z, a) - V[n + 1].double()).square().sum())
+            lam = M[n + 1].double()
+            ra += float((lam + 0.05 * (dact(z, a) * lam) @ k - M[n].double()).square().sum())
+        scale = float(V.double().norm() + M.double().norm())
+        for which, r in ((L.LP_STATE, rs), (L.LP_ADJOINT, ra)):
+            got = L.lp_residual_norm(p, which, K, b, V, M, ws)
+            assert abs(got - r ** 0.5) <= (q + 8) * EPS["f32"] * scale, (a, which)
