@@ -6,6 +6,8 @@ Tolerances are relative to the sums of absolute values: a sum of n products in
 working precision u, in any order, is within (n + 2) u of that; the bounds below
 use that with a factor 4 for the activation and the operand that feeds it.
 """
+import math
+
 import pytest
 import torch
 
@@ -299,3 +301,14 @@ def test_dense_residual_runs(q, N, B):
         for which, r in ((L.LP_STATE, rs), (L.LP_ADJOINT, ra)):
             got = L.lp_residual_norm(p, which, K, b, V, M, ws)
             assert abs(got - r ** 0.5) <= (q + 8) * EPS["f32"] * scale, (a, which)
+
+
+# one launch up to 8192 elements, partial sums above: fp64 sums of up to 2^17 products
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n", [0, 1, 1023, 1025, 8191, 8192, 8193, 131073])
+def test_vec_dot_sizes(dtype, n):
+    x, y = rnd(1, n, dtype=DT[dtype]), rnd(2, n, dtype=DT[dtype])
+    out = torch.full((1 + L.LP_DOT_PARTIALS,), float("nan"), device="cuda", dtype=torch.float64)
+    L.lp_vec_dot(x, y, out)
+    ref = (x.double() * y.double()).cpu()
+    assert abs(float(out[0]) - math.fsum(ref.tolist())) <= 32 * EPS["f64"] * float(ref.abs().sum())
