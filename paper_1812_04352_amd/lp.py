@@ -153,8 +153,10 @@ def traj_rows(p: "LpProblem", mg: Optional[LpMgrit] = None) -> int:
 # ---------------------------------------------------------------- tensor marshalling
 
 def _stream():
+    """The current stream of the current device, by its handle: an object for it
+    (torch.cuda.current_stream()) costs more than the rest of a vector call's checks."""
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _elem_dtype(p: LpProblem):
@@ -376,32 +378,45 @@ def lp_sgd_update(x, g, lr: float) -> None:
 LP_DOT_PARTIALS = 256
 
 
-def _vec_dtype(*ts):
+def _vec(x, y):
+    """Library dtype, length and device pointers of two vectors of one dtype and
+    length: the checks of _arr, each made once (an optimiser calls these functions
+    dozens of times an update on short vectors, so their host time counts)."""
     import torch
-    dt = ts[0].dtype
-    if dt not in (torch.float32, torch.float64) or any(t.dtype != dt for t in ts):
+    n, dt = y.numel(), x.dtype
+    if x.numel() != n:
+        raise ValueError("x and y differ in size")
+    if dt == torch.float32:
+        kind = LP_F32
+    elif dt == torch.float64:
+        kind = LP_F64
+    else:
+        kind = None
+    if kind is None or y.dtype != dt:
         raise ValueError("vectors must share dtype float32 or float64")
-    return LP_F32 if dt == torch.float32 else LP_F64
+    if not (x.is_cuda and y.is_cuda and x.is_contiguous() and y.is_contiguous()):
+        _arr(x, n, "x")
+        _arr(y, n, "y")
+    return kind, n, x.data_ptr(), y.data_ptr()
 
 
 def lp_vec_axpby(y, x, a: float, b: float) -> None:
     """y <- a x + b y over all elements (b = 0: y <- a x)."""
-    n = y.numel()
-    if x.numel() != n:
-        raise ValueError("x and y differ in size")
-    _check(load().lp_vec_axpby(_vec_dtype(x, y), n, a, _arr(x, n, "x"), b, _arr(y, n, "y"), _stream()),
-           "lp_vec_axpby")
+    kind, n, xp, yp = _vec(x, y)
+    rc = (_lib or load()).lp_vec_axpby(kind, n, a, xp, b, yp, _stream())
+    if rc:
+        _check(rc, "lp_vec_axpby")
 
 
 def lp_vec_dot(x, y, out) -> None:
     """out[0] <- x . y in fp64 (out: a device float64 tensor of 1 + LP_DOT_PARTIALS
     elements; the value is left on the device)."""
     import torch
-    n = x.numel()
-    if y.numel() != n:
-        raise ValueError("x and y differ in size")
-    _check(load().lp_vec_dot(_vec_dtype(x, y), n, _arr(x, n, "x"), _arr(y, n, "y"),
-                             _arr(out, 1 + LP_DOT_PARTIALS, "out", torch.float64), _stream()), "lp_vec_dot")
+    kind, n, xp, yp = _vec(x, y)
+    op = _arr(out, 1 + LP_DOT_PARTIALS, "out", torch.float64)
+    rc = (_lib or load()).lp_vec_dot(kind, n, xp, yp, op, _stream())
+    if rc:
+        _check(rc, "lp_vec_dot")
 
 
 def lp_accuracy(p: LpProblem, nc: int, uN, W, mu, c, acc, ws) -> None:
