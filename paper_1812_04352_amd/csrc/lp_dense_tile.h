@@ -1,7 +1,7 @@
 // Tiles of fp32 dense layers of width 32 or 64 on the matrix cores: the staged
 // weights, the per-lane layouts of a wave's examples with their products, and the
-// activations. Shared by the sweeps, serial solves and gradient (lp_dense_mfma.hip)
-// and the residual norms (lp_dense_resid.hip).
+// activations. Shared by the sweeps and gradient (lp_dense_mfma.hip), the serial
+// solves (lp_dense_serial.hip) and the residual norms (lp_dense_resid.hip).
 #pragma once
 
 #include <type_traits>
@@ -423,6 +423,27 @@ __device__ __forceinline__ void store_dsig(void* rec, size_t off, int act, const
   if (act == ACT_RELU) Lt::store_mask(static_cast<uint8_t*>(rec), off, d, on);
   else if (on) Lt::store(static_cast<float*>(rec) + off, d);
 }
+
+// A sigma' record row as loaded (16-example lanes): the example's word of ReLU's
+// decision bits (MaskWord) or the fp32 values of the smooth activations.
+template <typename Lt, bool BITS>
+struct RecRow;
+template <typename Lt>
+struct RecRow<Lt, true> {
+  static constexpr int Q = 16 * Lt::NB;
+  typename MaskWord<Q>::T w;
+  __device__ void load(const void* rec, size_t off) { w = MaskWord<Q>::load(static_cast<const uint8_t*>(rec), off); }
+  __device__ void get(typename Lt::V (&d)[Lt::NB]) const { Lt::unpack_mask(d, w, 4 * ((threadIdx.x & 63) >> 4)); }
+};
+template <typename Lt>
+struct RecRow<Lt, false> {
+  typename Lt::V v[Lt::NB];
+  __device__ void load(const void* rec, size_t off) { Lt::load(v, static_cast<const float*>(rec) + off); }
+  __device__ void get(typename Lt::V (&d)[Lt::NB]) const {
+#pragma unroll
+    for (int mb = 0; mb < Lt::NB; ++mb) d[mb] = v[mb];
+  }
+};
 
 // Fixed-order workgroup sum of one double per lane; result in thread 0.
 template <int WAVES>

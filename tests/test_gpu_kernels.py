@@ -312,3 +312,21 @@ def test_vec_dot_sizes(dtype, n):
     L.lp_vec_dot(x, y, out)
     ref = (x.double() * y.double()).cpu()
     assert abs(float(out[0]) - math.fsum(ref.tolist())) <= 32 * EPS["f64"] * float(ref.abs().sum())
+
+
+# serial solves with the operands of 4 (width 32) or 1 and 2 (width 64) layers in flight:
+# depths below, at and beside the rings' lengths; 16 examples per wave; weights through LDS
+# above 4096 (width 64) and 8192 examples. The bound is the narrow layers' above.
+@pytest.mark.parametrize("q", [32, 64])
+@pytest.mark.parametrize("N,batches", [(1, (1, 16, 33)), (2, (33,)), (3, (33,)), (4, (33,)), (5, (4097, 8193)),
+                                       (9, (33, 4096, 8193))])
+def test_dense_serial_depths(q, N, batches):
+    for B in batches:
+        for a in ("tanh", "smoothrelu", "identity"):
+            p, K, b, U, Lam = dense_problem("f32", q, a, N, B)
+            L.lp_serial_forward(p, K, b, U)
+            L.lp_serial_adjoint(p, K, b, U, Lam)
+            ref = serial_reference(K, b, U, Lam, a, 0.05)
+            for got, r in ((U, ref[0]), (Lam, ref[1])):
+                e = float((got.double() - r).norm() / r.norm())
+                assert e <= 16 * N * (q + 8) * EPS["f32"], (a, B, e)
