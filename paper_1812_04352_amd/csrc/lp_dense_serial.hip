@@ -5,10 +5,10 @@
 // batch there are few waves and the time per step is one wave's latency. Each
 // weight is used by one lane of a wave, in one product, so it goes from L1/L2
 // straight to the register that the matrix instruction reads; there is no LDS and
-// no barrier (with many waves per CU the weights go through LDS, below). Through LDS (written at the end of the step before, read back at the
-// start of the step) a step of width 32 took about 1300 cycles, of which its 16
-// matrix instructions take 512; 256 layers, 64 examples with opening and accuracy: 158
-// us before, 122 us now.
+// no barrier (with many waves per CU the weights go through LDS, below). Through LDS,
+// written at the end of the step before and read back at the start of the step, a
+// step of width 32 took about 1300 cycles, of which its 16 matrix instructions take
+// 512; 256 layers, 64 examples with opening and accuracy: 158 us before, 122 us now.
 // The operands of the next SER_D steps and their right-hand-side, sigma' record or
 // primal rows are in flight in register rings; every prefetch is issued
 // unconditionally with its index clamped to valid rows, so the number of loads in
