@@ -9,6 +9,7 @@
 
 #include "lp_device.h"
 #include "lp_internal.h"
+#include "lp_open_geo.h"
 
 namespace lp {
 namespace {
@@ -302,64 +303,63 @@ void open_grad_dense(const T* y, const T* L, const T* lam0, T* dL, int B, int q,
 // fp32 sums over a thread's pixels of one group, then fp64 in a fixed order.
 // 500 images of 28 x 28: 2245 us with one workgroup per channel and one pixel per
 // thread straight from memory (a chain of loads), 179 us now.
-constexpr int OCP = 8;             // pixels per thread and group
-constexpr int OC_LDS = 12 * 1024;  // floats of the haloed group
+using open_conv::OCP;
+using open_conv::OC_LDS;
+static_assert(open_conv::GNT == GNT, "threads of k_open_grad_conv");
 
 template <int ACT>
 __global__ __launch_bounds__(GNT) void k_open_grad_conv(const float* y, const float* L, const float* lam0, float* dL,
-                                                        int B, int C, int H, int W, int IM) {
+                                                        int B, int C, int H, int W) {
   __shared__ float img[OC_LDS];
   __shared__ double sh[GNT];
   const int co = blockIdx.x / 9, tap = blockIdx.x % 9, t = threadIdx.x;
-  const int P = H * W, PW = W + 2, PH = (H + 2) * PW;
+  const open_conv::Group g = open_conv::group(H, W);
+  const int P = g.P, PW = g.PW, IM = g.IM;
   float w[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) w[k] = L[co * 9 + k];
-  for (int i = t; i < IM * PH; i += GNT) img[i] = 0.f;
-  int at[OCP], gl[OCP], im[OCP];  // window corner in img, offset in lam0, image of the group
+  for (int i = t; i < IM * g.PH; i += GNT) img[i] = 0.f;
+  open_conv::Pixel px[OCP];
 #pragma unroll
-  for (int k = 0; k < OCP; ++k) {
-    const int i = t + k * GNT, p = i % P, yy = p / W;
-    im[k] = i / P;
-    if (im[k] >= IM) im[k] = B;  // none
-    at[k] = i / P * PH + yy * PW + (p - yy * W);
-    gl[k] = (i / P * C + co) * P + p;
-  }
+  for (int k = 0; k < OCP; ++k) px[k] = open_conv::pixel(g, W, C, co, t + k * GNT);
   const int toff = tap / 3 * PW + tap % 3;
   float yv[OCP], lv[OCP];
   auto fetch = [&](int e0) {
     const float* ye = y + (size_t)e0 * P;
     const float* le = lam0 + (size_t)e0 * C * P;
+    const int n = open_conv::images(g, B, e0);
 #pragma unroll
     for (int k = 0; k < OCP; ++k) {
-      const bool in = e0 + im[k] < B;
+      const bool in = open_conv::live(px[k], n);
       yv[k] = in ? ye[t + k * GNT] : 0.f;
-      lv[k] = in ? le[gl[k]] : 0.f;
+      lv[k] = in ? le[px[k].gl] : 0.f;
     }
   };
   fetch(0);
   double acc = 0.0;
-  for (int e0 = 0; e0 < B; e0 += IM) {
+  for (int e0 = 0;; e0 += IM) {
+    const int n = open_conv::images(g, B, e0);
     float lam[OCP];
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < OCP; ++k) {
       lam[k] = lv[k];
-      if (im[k] < IM) img[at[k] + PW + 1] = yv[k];
+      if (open_conv::stored(g, px[k])) img[open_conv::store_index(g, px[k])] = yv[k];
     }
     __syncthreads();
-    if (e0 + IM < B) fetch(e0 + IM);
+    if (B - e0 > IM) fetch(e0 + IM);
     float a = 0.f;
 #pragma unroll
     for (int k = 0; k < OCP; ++k) {
-      if (e0 + im[k] >= B) continue;
-      const float* q = img + at[k];
+      if (!open_conv::live(px[k], n)) continue;
+      const float* q = img + px[k].at;
       float z = 0.f;
 #pragma unroll
       for (int j = 0; j < 9; ++j) z = fma(w[j], q[j / 3 * PW + j % 3], z);
       a = fma(dact_f<float, ACT>(z) * lam[k], q[toff], a);
     }
     acc += (double)a;
+    if (B - e0 <= IM) break;
   }
   const double v = block_sum<GNT>(acc, sh);
   if (t == 0) dL[co * 9 + tap] = (float)v;
@@ -414,10 +414,9 @@ hipError_t open_grad_t(const Shape& s, int opening, int nf, int B, const void* y
     if (opening == 1) {
       open_grad_dense<T, ACT>((const T*)y, (const T*)L, (const T*)lam0, (T*)dL, B, q, nf, st);
     } else if constexpr (sizeof(T) == 4) {
-      const int IM = std::min(OCP * GNT / (s.H * s.W), OC_LDS / ((s.H + 2) * (s.W + 2)));
-      if (IM < 1) return hipErrorNotSupported;
+      if (open_conv::group(s.H, s.W).IM < 1) return hipErrorNotSupported;
       k_open_grad_conv<ACT><<<s.C * 9, GNT, 0, st>>>((const float*)y, (const float*)L, (const float*)lam0, (float*)dL,
-                                                     B, s.C, s.H, s.W, IM);
+                                                     B, s.C, s.H, s.W);
     } else {
       return hipErrorNotSupported;
     }
