@@ -110,31 +110,6 @@ __device__ __forceinline__ void gather_w(Split8 (&wr)[3], const float* sw, int l
   }
 }
 
-// The gradient's forward product (without a record) runs on the fp32 instruction
-// from an fp32 image: k-slice s of 24 and lane group g take ci = g + 4 (s / 12),
-// r = (s % 12) / 3, tx = s % 3, the same rows.
-__device__ __forceinline__ void gather_w32(float (&wr)[24], const float* sw, int lane) {
-  const int n = lane & 15, g = lane >> 4, co = n >> 1, dy = n & 1;
-#pragma unroll
-  for (int s = 0; s < 24; ++s) {
-    const int ci = g + 4 * (s / 12), r = (s % 12) / 3, tx = s % 3, ty = r - dy;
-    float w = 0.f;
-    if (ty >= 0 && ty <= 2) w = sw[co * 72 + ci * 9 + ty * 3 + tx];
-    wr[s] = w;
-  }
-}
-
-// acc += expanded weights x patches of the fp32 image for one tile
-__device__ __forceinline__ f32x4 conv_tile32(const float (&wr)[24], const float* buf, int base, int cs, int pw,
-                                             f32x4 acc) {
-#pragma unroll
-  for (int s = 0; s < 24; ++s) {
-    const int off = (s / 12) * 4 * cs + ((s % 12) / 3) * pw + (s % 3);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[s], buf[base + off], acc, 0, 0, 0);
-  }
-  return acc;
-}
-
 // ------------------------------------------------------------------ sweeps
 // One workgroup runs one example through one interval (or, serially, through a
 // whole level). The state being evolved lives in registers at the lane's own
@@ -178,13 +153,12 @@ __device__ __forceinline__ SGeo geo_of(const SGeo& ga) {
   else return make_geo(GH, GW);
 }
 
-// The lane's pair-pixel in tile t: patch origin (padded pixel; in the gradient's
-// fp32 image with the lane group's channel), own pixel in the split image (bytes) and
-// in the fp32 image, own output offset (register 0: channel 2*(lane/16), row 2Y,
-// column x) and whether it lies in the image; lanes past the last pair-pixel repeat
-// it and never write.
+// The lane's pair-pixel in tile t: patch origin (padded pixel), own pixel in the split
+// image (bytes) and in the gradient's fp32 image, own output offset (register 0:
+// channel 2*(lane/16), row 2Y, column x) and whether it lies in the image; lanes past
+// the last pair-pixel repeat it and never write.
 struct Px {
-  int base, base32, own, lds, gl;
+  int base, own, lds, gl;
   bool ok;
 };
 
@@ -195,7 +169,6 @@ __device__ __forceinline__ Px px_of(const SGeo& g, int t, int lane) {
   if (!p.ok) P = g.NPP - 1;
   const int Y = P / g.W, x = P - Y * g.W, grp = lane >> 4;
   p.base = 2 * Y * g.PW + x;
-  p.base32 = grp * g.CS + p.base;
   p.own = 16 * (p.base + g.PW + 1) + 4 * grp;
   p.lds = 2 * grp * g.CS + p.base + g.PW + 1;
   p.gl = 2 * grp * g.HW + 2 * Y * g.W + x;
@@ -241,17 +214,30 @@ __device__ __forceinline__ void put_px(char* buf, f32x4 v, const SGeo& g, const 
   }
 }
 
-// Products of the wave's tiles from the split image, z[tt] = init + weights x
-// patches, the smallest partial products first.
+// Offset, in padded pixels, of the window position that the lane's group holds in slice s.
+__device__ __forceinline__ int slice_off(const SGeo& g, int s, int lane) {
+  const int q = 4 * s + (lane >> 4), r = q / 3;
+  return r * g.PW + q - 3 * r;
+}
+
+// Product of one tile from its operand fragments, init + weights x patches, the
+// smallest partial products first.
+__device__ __forceinline__ f32x4 conv_mma(const Split8 (&wr)[3], const Split8 (&b)[3], f32x4 acc) {
+  constexpr int ia[6] = {0, 2, 1, 0, 1, 0}, ib[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+  for (int k = 0; k < 6; ++k)
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[s].p[ia[k]], b[s].p[ib[k]], acc, 0, 0, 0);
+  return acc;
+}
+
+// Products of the wave's tiles from the split image.
 __device__ __forceinline__ void conv_tiles(f32x4 (&z)[TPW], const Split8 (&wr)[3], const char* buf, const SGeo& g,
                                            int t0, int lane, f32x4 init) {
-  constexpr int ia[6] = {0, 2, 1, 0, 1, 0}, ib[6] = {2, 0, 1, 1, 0, 0};
   int off[3];
 #pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    const int q = 4 * s + (lane >> 4), r = q / 3;
-    off[s] = 16 * (r * g.PW + q - 3 * r);
-  }
+  for (int s = 0; s < 3; ++s) off[s] = 16 * slice_off(g, s, lane);
 #pragma unroll
   for (int tt = 0; tt < TPW; ++tt) {
     const char* src = buf + 16 * px_of(g, t0 + tt, lane).base;
@@ -261,13 +247,29 @@ __device__ __forceinline__ void conv_tiles(f32x4 (&z)[TPW], const Split8 (&wr)[3
 #pragma unroll
       for (int part = 0; part < 3; ++part)
         b[s].p[part] = *reinterpret_cast<const bf16x8*>(src + off[s] + part * g.PS);
-    f32x4 acc = init;
+    z[tt] = conv_mma(wr, b, init);
+  }
+}
+
+// The same products, bit for bit, from the gradient's fp32 image: the operand is
+// split as it is read.
+__device__ __forceinline__ void conv_tiles32(f32x4 (&z)[TPW], const Split8 (&wr)[3], const float* buf, const SGeo& g,
+                                             int t0, int lane, f32x4 init) {
+  int off[3];
 #pragma unroll
-    for (int k = 0; k < 6; ++k)
+  for (int s = 0; s < 3; ++s) off[s] = slice_off(g, s, lane);
 #pragma unroll
-      for (int s = 0; s < 3; ++s)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[s].p[ia[k]], b[s].p[ib[k]], acc, 0, 0, 0);
-    z[tt] = acc;
+  for (int tt = 0; tt < TPW; ++tt) {
+    const float* src = buf + px_of(g, t0 + tt, lane).base;
+    Split8 b[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      f32x8 x;
+#pragma unroll
+      for (int ci = 0; ci < CH; ++ci) x[ci] = src[ci * g.CS + off[s]];
+      b[s] = split8(x);
+    }
+    z[tt] = conv_mma(wr, b, init);
   }
 }
 
@@ -964,7 +966,8 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
   float* bu = lds;                   // CH * CS: u
   float* bs = lds + CH * g.CS;       // CH * CS: s
   float* sw = lds + 2 * CH * g.CS;   // the layer's weights
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t0 = wave * TPW, nt = blockDim.x;
+  int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6, t0 = wave * TPW, nt = blockDim.x;
   const int n = blockIdx.x, chunk = blockIdx.y;
   const int per = (a.B + a.nchunks - 1) / a.nchunks;
   const int e0 = chunk * per, e1 = min(a.B, e0 + per);
@@ -999,9 +1002,10 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
     if constexpr (REC) rw = rec_load<RB>(a.dsig, (size_t)n * a.B + e0, g, t0, lane);
   }
   __syncthreads();  // buffers zeroed, weights staged
-  float wf[24];
-  gather_w32(wf, sw, lane);
-  const f32x4 bias = bias_px(sw, lane);
+  const float sgn = layer_sign(n);
+  Split8 wf[3];
+  if constexpr (!REC) gather_w<false>(wf, sw, lane, sgn);
+  const f32x4 bias = sgn * bias_px(sw, lane);
   // s = sigma' * lam at the lane's own pixels into the s image, and into db
   auto put_s = [&](const f32x4 (&z)[TPW]) {
 #pragma unroll
@@ -1049,12 +1053,14 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
   for (int e = e0; e < e1; ++e) {
     const bool more = e + 1 < e1;
     if constexpr (!REC) {
+      // tile offsets are recomputed for each example (see k_fwd)
+      asm volatile("" : "+v"(lane));
       f32x4 z[TPW];
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) lam[tt] = ld_px(Lm + (size_t)e * g.q, g, px_of(g, t0 + tt, lane));
+      conv_tiles32(z, wf, bu, g, t0, lane, bias);
 #pragma unroll
-      for (int tt = 0; tt < TPW; ++tt)
-        z[tt] = conv_tile32(wf, bu, px_of(g, t0 + tt, lane).base32, g.CS, g.PW, bias);
+      for (int tt = 0; tt < TPW; ++tt) z[tt] *= sgn;
       act_tiles<true>(z, a.act);
       put_s(z);
       __syncthreads();
