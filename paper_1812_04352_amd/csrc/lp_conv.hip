@@ -175,6 +175,52 @@ __device__ __forceinline__ Px px_of(const SGeo& g, int t, int lane) {
   return p;
 }
 
+// The pair-pixels of a wave's tiles t0 .. t0 + TPW - 1. With a compile-time geometry
+// they are computed where they are used (multiplications by constants). With a
+// run-time one that takes a division per tile, and keeping every offset instead takes
+// more registers than there are: here a tile is one packed word, its patch origin and
+// output pixel (a supported image has at most 988 padded pixels), and the offsets are
+// additions to these. Scratch of the 40 run-time sweep instances, bytes per lane: 10100
+// with divisions, 280 so; 256 images of 20 x 27, 64 layers, three levels, two
+// iterations, us: forward with a record 2011 and 1307, adjoint without one 8205 and 2511.
+template <int GH>
+struct Tiles {
+  int t0;
+  __device__ Tiles(const SGeo&, int t0, int) : t0(t0) {}
+  __device__ Px operator()(const SGeo& g, int tt, int lane) const { return px_of(g, t0 + tt, lane); }
+  __device__ void opaque() {}
+};
+template <>
+struct Tiles<0> {
+  int t0;
+  uint32_t w[TPW];  // bits 0-11 the patch origin, 12-23 the output pixel, 31 set past the image
+  __device__ Tiles(const SGeo& g, int t0, int lane) : t0(t0) {
+#pragma unroll
+    for (int tt = 0; tt < TPW; ++tt) {
+      int P = 16 * (t0 + tt) + (lane & 15);
+      const bool ok = P < g.NPP;
+      if (!ok) P = g.NPP - 1;
+      const int Y = P / g.W, x = P - Y * g.W;
+      w[tt] = (uint32_t)(2 * Y * g.PW + x) | (uint32_t)(2 * Y * g.W + x) << 12 | (ok ? 0u : 1u << 31);
+    }
+  }
+  __device__ Px operator()(const SGeo& g, int tt, int lane) const {
+    const int grp = lane >> 4;
+    Px p;
+    p.ok = (int)w[tt] >= 0;
+    p.base = (int)(w[tt] & 0xfffu);
+    p.own = 16 * (p.base + g.PW + 1) + 4 * grp;
+    p.lds = 2 * grp * g.CS + p.base + g.PW + 1;
+    p.gl = 2 * grp * g.HW + (int)(w[tt] >> 12 & 0xfffu);
+    return p;
+  }
+  // the offsets derived from the words are formed anew after this point, not kept
+  __device__ void opaque() {
+#pragma unroll
+    for (int tt = 0; tt < TPW; ++tt) asm volatile("" : "+v"(w[tt]));
+  }
+};
+
 // accumulator register r: channel 2*(lane/16) + r/2, row 2Y + r%2
 __device__ __forceinline__ int lds_r(const SGeo& g, const Px& p, int r) { return p.lds + (r >> 1) * g.CS + (r & 1) * g.PW; }
 __device__ __forceinline__ int gl_r(const SGeo& g, const Px& p, int r) { return p.gl + (r >> 1) * g.HW + (r & 1) * g.W; }
@@ -233,14 +279,15 @@ __device__ __forceinline__ f32x4 conv_mma(const Split8 (&wr)[3], const Split8 (&
 }
 
 // Products of the wave's tiles from the split image.
+template <class TL>
 __device__ __forceinline__ void conv_tiles(f32x4 (&z)[TPW], const Split8 (&wr)[3], const char* buf, const SGeo& g,
-                                           int t0, int lane, f32x4 init) {
+                                           const TL& tl, int lane, f32x4 init) {
   int off[3];
 #pragma unroll
   for (int s = 0; s < 3; ++s) off[s] = 16 * slice_off(g, s, lane);
 #pragma unroll
   for (int tt = 0; tt < TPW; ++tt) {
-    const char* src = buf + 16 * px_of(g, t0 + tt, lane).base;
+    const char* src = buf + 16 * tl(g, tt, lane).base;
     Split8 b[3];
 #pragma unroll
     for (int s = 0; s < 3; ++s)
@@ -253,14 +300,15 @@ __device__ __forceinline__ void conv_tiles(f32x4 (&z)[TPW], const Split8 (&wr)[3
 
 // The same products, bit for bit, from the gradient's fp32 image: the operand is
 // split as it is read.
+template <class TL>
 __device__ __forceinline__ void conv_tiles32(f32x4 (&z)[TPW], const Split8 (&wr)[3], const float* buf, const SGeo& g,
-                                             int t0, int lane, f32x4 init) {
+                                             const TL& tl, int lane, f32x4 init) {
   int off[3];
 #pragma unroll
   for (int s = 0; s < 3; ++s) off[s] = slice_off(g, s, lane);
 #pragma unroll
   for (int tt = 0; tt < TPW; ++tt) {
-    const float* src = buf + px_of(g, t0 + tt, lane).base;
+    const float* src = buf + tl(g, tt, lane).base;
     Split8 b[3];
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
@@ -443,7 +491,7 @@ __device__ __forceinline__ Blk sweep_block() {
 // SIMD leave room for it).
 template <int MODE, int GH, int GW, int RK, bool HG>
 __global__ __launch_bounds__(64 * MAXW)
-__attribute__((amdgpu_waves_per_eu(MODE == SWEEP_CORRF && RK == 1 ? 2 : 3, 8)))
+__attribute__((amdgpu_waves_per_eu(MODE == SWEEP_CORRF && (RK == 1 || (RK == 2 && GH == 0)) ? 2 : 3, 8)))
 void k_fwd(SweepArgs a, SGeo ga) {
   constexpr bool REC = RK != 0, RB = RK == 1;
   // weight entries per thread while staging (the specialised geometry fixes the thread count)
@@ -457,6 +505,7 @@ void k_fwd(SweepArgs a, SGeo ga) {
   // the wave's first tile, uniform across the wave, so the tile bases derived from it
   // live in scalar registers
   const int t0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) * TPW, nt = blockDim.x;
+  Tiles<GH> tl(g, t0, lane);
   const Blk wb = sweep_block();
   const int k = wb.k, Nc = gridDim.x;
   const size_t slice = (size_t)a.B * g.q, eo = (size_t)wb.ex * g.q;
@@ -494,18 +543,18 @@ void k_fwd(SweepArgs a, SGeo ga) {
     // vsrc inside the tile loop splits it into one wait per tile (measured 4.8 %
     // faster here; the FC sweep measured slower with it and keeps the tile loop)
 #pragma unroll
-    for (int tt = 0; tt < TPW; ++tt) v[tt] = ld_px(src, g, px_of(g, t0 + tt, lane));
+    for (int tt = 0; tt < TPW; ++tt) v[tt] = ld_px(src, g, tl(g, tt, lane));
     if (vsrc) {
       f32x4 cv[TPW];
 #pragma unroll
-      for (int tt = 0; tt < TPW; ++tt) cv[tt] = ld_px(vsrc, g, px_of(g, t0 + tt, lane));
+      for (int tt = 0; tt < TPW; ++tt) cv[tt] = ld_px(vsrc, g, tl(g, tt, lane));
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) v[tt] = v[tt] + (cv[tt] - v[tt]);
     }
   } else {
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       v[tt] = ld_px(src, g, p);
       if (vsrc) v[tt] = v[tt] + (ld_px(vsrc, g, p) - v[tt]);
     }
@@ -513,7 +562,7 @@ void k_fwd(SweepArgs a, SGeo ga) {
   __syncthreads();  // halo zeroed
 #pragma unroll
   for (int tt = 0; tt < TPW; ++tt) {
-    const Px p = px_of(g, t0 + tt, lane);
+    const Px p = tl(g, tt, lane);
     if (p.ok) {
       put_px(buf, v[tt], g, p);
       if (MODE == SWEEP_CORRF && k > 0) st_px(X + kc * slice + eo, v[tt], g, p);
@@ -537,6 +586,7 @@ void k_fwd(SweepArgs a, SGeo ga) {
     // tile offsets derived from it are recomputed each step instead of being kept
     // live in registers through the loop (fewer registers, more resident waves)
     asm volatile("" : "+v"(lane));
+    tl.opaque();
     const float* swc = sw + (j & 1) * WV;
     const size_t nxt = (size_t)(kc + (j + 1 < nsteps ? j + 1 : j + extra)) * a.stride;
     float wreg[WPT];
@@ -544,13 +594,13 @@ void k_fwd(SweepArgs a, SGeo ga) {
     f32x4 z[TPW], gv[HG ? TPW : 1];
     if constexpr (HG) {
 #pragma unroll
-      for (int tt = 0; tt < TPW; ++tt) gv[tt] = ld_px(G + (kc + j + 1) * slice + eo, g, px_of(g, t0 + tt, lane));
+      for (int tt = 0; tt < TPW; ++tt) gv[tt] = ld_px(G + (kc + j + 1) * slice + eo, g, tl(g, tt, lane));
     }
     {
       const float sgn = layer_sign((size_t)(kc + j) * a.stride);
       Split8 wr[3];
       gather_w<false>(wr, swc, lane, sgn);
-      conv_tiles(z, wr, buf, g, t0, lane, sgn * bias_px(swc, lane));
+      conv_tiles(z, wr, buf, g, tl, lane, sgn * bias_px(swc, lane));
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) z[tt] *= sgn;
     }
@@ -565,17 +615,17 @@ void k_fwd(SweepArgs a, SGeo ga) {
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
       if (MODE == SWEEP_FRES && j == 0) {
-        const Px p = px_of(g, t0 + tt, lane);
+        const Px p = tl(g, tt, lane);
         if (p.ok) st_px(gn, v[tt] + hc * z[tt], g, p);
       }
       v[tt] = v[tt] + hl * z[tt];
       if constexpr (HG) v[tt] += gv[tt];
-      else if (gi) v[tt] += ld_px(gi, g, px_of(g, t0 + tt, lane));
+      else if (gi) v[tt] += ld_px(gi, g, tl(g, tt, lane));
     }
     __syncthreads();  // every read of the step's input is done
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (p.ok) {
         put_px(buf, v[tt], g, p);
         if (MODE == SWEEP_CORRF || MODE == MODE_SERIAL) st_px(X + (kc + j + 1) * slice + eo, v[tt], g, p);
@@ -593,7 +643,7 @@ void k_fwd(SweepArgs a, SGeo ga) {
     const float sgn = layer_sign((size_t)(kc + nsteps) * a.stride);
     Split8 wr[3];
     gather_w<false>(wr, swc, lane, sgn);
-    conv_tiles(z, wr, buf, g, t0, lane, sgn * bias_px(swc, lane));
+    conv_tiles(z, wr, buf, g, tl, lane, sgn * bias_px(swc, lane));
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) z[tt] *= sgn;
     const size_t blk = (size_t)(kc + nsteps) * a.stride * a.B + wb.ex;
@@ -603,7 +653,7 @@ void k_fwd(SweepArgs a, SGeo ga) {
     float* so = static_cast<float*>(a.S) + (size_t)(k + 1) * slice + eo;
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (p.ok) st_px(so, v[tt], g, p);
     }
   } else if (MODE == SWEEP_FRES) {
@@ -613,13 +663,13 @@ void k_fwd(SweepArgs a, SGeo ga) {
     f32x4 cv[TPW], pk[TPW];
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       cv[tt] = ld_px(cn, g, p);
       pk[tt] = ld_px(gn, g, p);  // this lane's own step-0 stores (ghost lanes: unused)
     }
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (p.ok) {
         const f32x4 rr = v[tt] - cv[tt];
 #pragma unroll
@@ -652,6 +702,9 @@ __global__ __launch_bounds__(64 * MAXW)
 __attribute__((amdgpu_waves_per_eu(RK == 0 || (RK == 2 && (MODE == SWEEP_CORRF || MODE == MODE_SERIAL)) ? 2 : 3, 8)))
 void k_adj(SweepArgs a, SGeo ga) {
   constexpr bool REC = RK != 0, RB = RK == 1;
+  // right-hand-side rows are requested before the product (without a record and with
+  // a run-time geometry there is no room for them)
+  constexpr bool AHEAD = HG && !(GH == 0 && RK == 0);
   // weight entries per thread while staging (the specialised geometry fixes the thread count)
   constexpr int WPT = GH ? (WV + 64 * make_geo(GH, GW).NW - 1) / (64 * make_geo(GH, GW).NW) : (WV + 63) / 64;
   const SGeo g = geo_of<GH, GW>(ga);
@@ -666,6 +719,7 @@ void k_adj(SweepArgs a, SGeo ga) {
   constexpr bool UNIF = (MODE == SWEEP_FRES || MODE == SWEEP_FC) && RK != 0;
   const int wave = threadIdx.x >> 6;
   const int t0 = (UNIF ? __builtin_amdgcn_readfirstlane(wave) : wave) * TPW, nt = blockDim.x;
+  Tiles<GH> tl(g, t0, lane);
   const Blk wb = sweep_block();
   const int k = wb.k, Nc = gridDim.x;
   const size_t slice = (size_t)a.B * g.q, eo = (size_t)wb.ex * g.q;
@@ -703,21 +757,21 @@ void k_adj(SweepArgs a, SGeo ga) {
   f32x4 lam[TPW], un[TPW];
 #pragma unroll
   for (int tt = 0; tt < TPW; ++tt) {
-    const Px p = px_of(g, t0 + tt, lane);
+    const Px p = tl(g, tt, lane);
     lam[tt] = ld_px(src, g, p);
     if (!REC) un[tt] = ld_px(Uf + (size_t)(top - 1) * ustep + eo, g, p);
   }
   if (vsrc) {
     f32x4 cv[TPW];
 #pragma unroll
-    for (int tt = 0; tt < TPW; ++tt) cv[tt] = ld_px(vsrc, g, px_of(g, t0 + tt, lane));
+    for (int tt = 0; tt < TPW; ++tt) cv[tt] = ld_px(vsrc, g, tl(g, tt, lane));
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) lam[tt] = lam[tt] + (cv[tt] - lam[tt]);
   }
   __syncthreads();  // halo zeroed
 #pragma unroll
   for (int tt = 0; tt < TPW; ++tt) {
-    const Px p = px_of(g, t0 + tt, lane);
+    const Px p = tl(g, tt, lane);
     if (p.ok) {
       if (!REC) put_px(buf, un[tt], g, p);
       if (MODE == SWEEP_CORRF && k + 1 < Nc) st_px(X + top * slice + eo, lam[tt], g, p);
@@ -732,16 +786,21 @@ void k_adj(SweepArgs a, SGeo ga) {
   if constexpr (REC) rn = rec_load<RB>(a.dsig, (size_t)(top - 1) * a.stride * a.B + wb.ex, g, t0, lane);
   for (int j = 0; j < nsteps; ++j) {
     // tile offsets recomputed each step (see k_fwd) where that lowers the
-    // register count (compiler-measured per variant)
-    constexpr bool OPAQUE = REC ? (MODE == SWEEP_FC || MODE == SWEEP_FRES) : MODE != SWEEP_FRES;
+    // register count (compiler-measured per variant; always with a run-time geometry)
+    constexpr bool OPAQUE = GH == 0 || (REC ? (MODE == SWEEP_FC || MODE == SWEEP_FRES) : MODE != SWEEP_FRES);
     if constexpr (OPAQUE) asm volatile("" : "+v"(lane));
+    tl.opaque();
     const long i = top - 1 - j;
     const float sgn = layer_sign((size_t)i * a.stride);
     const bool more = j + 1 < nsteps;
     const float* swc = sw + (j & 1) * WV;
-    // the coarse correction and serial sweeps with ReLU's bits stage in one go: their
-    // registers are spoken for
-    constexpr bool SPLIT = !(RK == 1 && HG && (MODE == SWEEP_CORRF || MODE == MODE_SERIAL));
+    // Where the registers are spoken for, the next weights are staged in one go. At
+    // 28 x 28: the coarse correction and serial sweeps with ReLU's bits. With a
+    // run-time geometry (a thread carries up to 10 weights, not 3): the coarse levels,
+    // the fp32 record, and without a record FRES and the serial solve.
+    constexpr bool SPLIT =
+        GH == 0 ? !HG && (RK == 1 || (RK == 0 && MODE != SWEEP_FRES && MODE != MODE_SERIAL))
+                : !(HG && RK == 1 && (MODE == SWEEP_CORRF || MODE == MODE_SERIAL));
     float wreg[SPLIT ? WPT : 1];
     if constexpr (SPLIT) stage_fetch<WPT>(wreg, K, bb, (size_t)(more ? i - 1 : i) * a.stride, nt);
     else stage_w(sw + ((j & 1) ^ 1) * WV, K, bb, (size_t)(more ? i - 1 : i) * a.stride, nt);
@@ -753,7 +812,7 @@ void k_adj(SweepArgs a, SGeo ga) {
     } else {
       Split8 wr[3];
       gather_w<false>(wr, swc, lane, sgn);
-      conv_tiles(dd, wr, buf, g, t0, lane, sgn * bias_px(swc, lane));
+      conv_tiles(dd, wr, buf, g, tl, lane, sgn * bias_px(swc, lane));
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) dd[tt] *= sgn;
       act_tiles<true>(dd, a.act);
@@ -765,28 +824,28 @@ void k_adj(SweepArgs a, SGeo ga) {
     if (!REC) __syncthreads();
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (p.ok) put_px(buf, dd[tt] * lam[tt], g, p);
     }
     __syncthreads();
     // the next step's primal state arrives while the transposed product runs
     if (!REC && more) {
 #pragma unroll
-      for (int tt = 0; tt < TPW; ++tt) un[tt] = ld_px(Uf + (size_t)(i - 1) * ustep + eo, g, px_of(g, t0 + tt, lane));
+      for (int tt = 0; tt < TPW; ++tt) un[tt] = ld_px(Uf + (size_t)(i - 1) * ustep + eo, g, tl(g, tt, lane));
     }
-    f32x4 w[TPW], gv[HG ? TPW : 1];
-    if constexpr (HG) {
+    f32x4 w[TPW], gv[AHEAD ? TPW : 1];
+    if constexpr (AHEAD) {
 #pragma unroll
-      for (int tt = 0; tt < TPW; ++tt) gv[tt] = ld_px(G + (size_t)i * slice + eo, g, px_of(g, t0 + tt, lane));
+      for (int tt = 0; tt < TPW; ++tt) gv[tt] = ld_px(G + (size_t)i * slice + eo, g, tl(g, tt, lane));
     }
-    conv_tiles(w, wt, buf, g, t0, lane, f32x4{0.f, 0.f, 0.f, 0.f});
-    const float* gi = !HG && G ? G + (size_t)i * slice + eo : nullptr;
+    conv_tiles(w, wt, buf, g, tl, lane, f32x4{0.f, 0.f, 0.f, 0.f});
+    const float* gi = !AHEAD && G ? G + (size_t)i * slice + eo : nullptr;
     float* xo = (MODE == SWEEP_CORRF || MODE == MODE_SERIAL) ? X + (size_t)i * slice + eo : nullptr;
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       lam[tt] = lam[tt] + (sgn * hl) * w[tt];
-      if constexpr (HG) lam[tt] += gv[tt];
+      if constexpr (AHEAD) lam[tt] += gv[tt];
       else if (gi) lam[tt] += ld_px(gi, g, p);
       if (xo && p.ok) st_px(xo, lam[tt], g, p);
     }
@@ -796,7 +855,7 @@ void k_adj(SweepArgs a, SGeo ga) {
       if (more) {
 #pragma unroll
         for (int tt = 0; tt < TPW; ++tt) {
-          const Px p = px_of(g, t0 + tt, lane);
+          const Px p = tl(g, tt, lane);
           if (p.ok) put_px(buf, un[tt], g, p);
         }
       }
@@ -808,7 +867,7 @@ void k_adj(SweepArgs a, SGeo ga) {
     float* so = static_cast<float*>(a.S) + (size_t)k * slice + eo;
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (p.ok) st_px(so, lam[tt], g, p);
     }
   } else if (MODE == SWEEP_FRES) {
@@ -820,14 +879,14 @@ void k_adj(SweepArgs a, SGeo ga) {
     f32x4 cu[TPW], cl[TPW];
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       cu[tt] = ld_px(src, g, p);
       cl[tt] = ld_px(ck, g, p);
     }
     double acc = 0.0;
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       // with the record, sigma' of the last step comes from its words, still in
       // registers (the loop requests no further step after the last)
       const f32x4 d = REC ? rec_val<RB>(rn, tt) : dd[tt];
@@ -843,13 +902,13 @@ void k_adj(SweepArgs a, SGeo ga) {
     gather_w<true>(wt, sw, lane, sgn);
     __syncthreads();
     f32x4 w[TPW];
-    conv_tiles(w, wt, buf, g, t0, lane, f32x4{0.f, 0.f, 0.f, 0.f});
+    conv_tiles(w, wt, buf, g, tl, lane, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) cu[tt] += (sgn * hc) * w[tt];
     float* gn = static_cast<float*>(a.Gn) + (size_t)k * slice + eo;
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (p.ok) st_px(gn, lam[tt] - cu[tt], g, p);  // g_{l+1}^k = f_k - Phibar_{l+1}(C_{k+1})
     }
     if (a.xn_every > 0 && k % a.xn_every == 0) row_copy(static_cast<float*>(a.Xn) + (size_t)k * slice + eo, ck, g.q, nt);
@@ -878,6 +937,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resid(ResidArgs a, SGeo g) {
   float* sw = lds + 3 * g.PS / 4;            // the layer's weights
   __shared__ double red[MAXW];
   const int lane = threadIdx.x & 63, t0 = (threadIdx.x >> 6) * TPW, nt = blockDim.x;
+  const Tiles<0> tl(g, t0, lane);
   const int n = blockIdx.x;
   const size_t slice = (size_t)a.B * g.q, eo = (size_t)blockIdx.y * g.q;
   const float* U = static_cast<const float*>(a.U);
@@ -887,11 +947,11 @@ __global__ __launch_bounds__(64 * MAXW) void k_resid(ResidArgs a, SGeo g) {
   stage_w(sw, static_cast<const float*>(a.K), static_cast<const float*>(a.b), n, nt);
   f32x4 un[TPW];
 #pragma unroll
-  for (int tt = 0; tt < TPW; ++tt) un[tt] = ld_px(U + (size_t)n * slice + eo, g, px_of(g, t0 + tt, lane));
+  for (int tt = 0; tt < TPW; ++tt) un[tt] = ld_px(U + (size_t)n * slice + eo, g, tl(g, tt, lane));
   __syncthreads();  // halo zeroed, weights staged
 #pragma unroll
   for (int tt = 0; tt < TPW; ++tt) {
-    const Px p = px_of(g, t0 + tt, lane);
+    const Px p = tl(g, tt, lane);
     if (p.ok) put_px(buf, un[tt], g, p);
   }
   __syncthreads();
@@ -900,7 +960,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resid(ResidArgs a, SGeo g) {
   {
     Split8 wr[3];
     gather_w<false>(wr, sw, lane, sgn);
-    conv_tiles(z, wr, buf, g, t0, lane, sgn * bias_px(sw, lane));
+    conv_tiles(z, wr, buf, g, tl, lane, sgn * bias_px(sw, lane));
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) z[tt] *= sgn;
   }
@@ -909,7 +969,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_resid(ResidArgs a, SGeo g) {
     act_tiles<false>(z, a.act);
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (!p.ok) continue;
       const f32x4 rr = (un[tt] + h * z[tt]) - ld_px(U + (size_t)(n + 1) * slice + eo, g, p);
 #pragma unroll
@@ -919,21 +979,21 @@ __global__ __launch_bounds__(64 * MAXW) void k_resid(ResidArgs a, SGeo g) {
     act_tiles<true>(z, a.act);
     f32x4 lam[TPW];
 #pragma unroll
-    for (int tt = 0; tt < TPW; ++tt) lam[tt] = ld_px(Lm + (size_t)(n + 1) * slice + eo, g, px_of(g, t0 + tt, lane));
+    for (int tt = 0; tt < TPW; ++tt) lam[tt] = ld_px(Lm + (size_t)(n + 1) * slice + eo, g, tl(g, tt, lane));
     __syncthreads();  // every read of U[n] is done
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (p.ok) put_px(buf, z[tt] * lam[tt], g, p);
     }
     __syncthreads();
     Split8 wt[3];
     gather_w<true>(wt, sw, lane, sgn);
     f32x4 w[TPW];
-    conv_tiles(w, wt, buf, g, t0, lane, f32x4{0.f, 0.f, 0.f, 0.f});
+    conv_tiles(w, wt, buf, g, tl, lane, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (!p.ok) continue;
       const f32x4 rr = (lam[tt] + (sgn * h) * w[tt]) - ld_px(Lm + (size_t)n * slice + eo, g, p);
 #pragma unroll
@@ -968,6 +1028,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
   float* sw = lds + 2 * CH * g.CS;   // the layer's weights
   int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6, t0 = wave * TPW, nt = blockDim.x;
+  Tiles<GH> tl(g, t0, lane);
   const int n = blockIdx.x, chunk = blockIdx.y;
   const int per = (a.B + a.nchunks - 1) / a.nchunks;
   const int e0 = chunk * per, e1 = min(a.B, e0 + per);
@@ -995,7 +1056,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
   if (e0 < e1) {
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       un[tt] = ld_px(U + (size_t)e0 * g.q, g, p);
       if constexpr (REC) lam[tt] = ld_px(Lm + (size_t)e0 * g.q, g, p);
     }
@@ -1010,7 +1071,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
   auto put_s = [&](const f32x4 (&z)[TPW]) {
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (p.ok) {
         const f32x4 s = z[tt] * lam[tt];
         put_px32(bs, s, g, p);
@@ -1044,7 +1105,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
   if (e0 < e1) {
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
-      const Px p = px_of(g, t0 + tt, lane);
+      const Px p = tl(g, tt, lane);
       if (p.ok) put_px32(bu, un[tt], g, p);
     }
     if constexpr (REC) put_rec_s();
@@ -1055,10 +1116,11 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
     if constexpr (!REC) {
       // tile offsets are recomputed for each example (see k_fwd)
       asm volatile("" : "+v"(lane));
+      tl.opaque();
       f32x4 z[TPW];
 #pragma unroll
-      for (int tt = 0; tt < TPW; ++tt) lam[tt] = ld_px(Lm + (size_t)e * g.q, g, px_of(g, t0 + tt, lane));
-      conv_tiles32(z, wf, bu, g, t0, lane, bias);
+      for (int tt = 0; tt < TPW; ++tt) lam[tt] = ld_px(Lm + (size_t)e * g.q, g, tl(g, tt, lane));
+      conv_tiles32(z, wf, bu, g, tl, lane, bias);
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) z[tt] *= sgn;
       act_tiles<true>(z, a.act);
@@ -1070,7 +1132,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
     if (more) {
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) {
-        const Px p = px_of(g, t0 + tt, lane);
+        const Px p = tl(g, tt, lane);
         un[tt] = ld_px(U + (size_t)(e + 1) * g.q, g, p);
         if constexpr (REC) lam[tt] = ld_px(Lm + (size_t)(e + 1) * g.q, g, p);
       }
@@ -1097,7 +1159,7 @@ __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
     if (more) {
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) {
-        const Px p = px_of(g, t0 + tt, lane);
+        const Px p = tl(g, tt, lane);
         if (p.ok) put_px32(bu, un[tt], g, p);
       }
       if constexpr (REC) put_rec_s();
