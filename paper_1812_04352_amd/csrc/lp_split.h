@@ -26,17 +26,13 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lp_layer_sign.h"
+
 namespace lp {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float split_f32x4 __attribute__((ext_vector_type(4)));
-
-// -1 for layers with an odd number of one bits, which alternates evenly on the
-// layers n = 0, c^l, 2 c^l, .. of every level l too
-__device__ __forceinline__ float layer_sign(size_t n) {
-  return __builtin_popcountll((unsigned long long)n) & 1 ? -1.f : 1.f;
-}
 
 // Eight values of a lane, split.
 struct Split8 {
