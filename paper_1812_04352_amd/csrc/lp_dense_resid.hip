@@ -5,11 +5,13 @@
 // 64 examples (a wave 16) through a run of consecutive layers, so that a layer's
 // output row is the next one's input and is read once; the next layer's weights and
 // rows are requested before the current products, and LDS holds two layers. The
-// arithmetic of a step is that of the sweeps and serial solves.
+// arithmetic of a step is that of the sweeps and serial solves, but for tanh.
 //
 // One thread per example evaluated all Q activations and Q^2 products in a row and
-// read every row twice. 512 layers of width 64, 4096 examples (0.54 GB of states):
-// RATE_STATE, RATE_ADJ.
+// read every row twice. 512 layers of width 64, 4096 examples (0.54 GB of states), tanh,
+// with the reduction and the read-back: state 562 us then, 245 now; adjoint 904 and 392
+// (ReLU 471 and 196, 793 and 329). The state's rows are read once at 2.2 TB/s with
+// tanh, 2.7 with ReLU: bound by the vector ALU, then by the fp32 matrix rate.
 #include <algorithm>
 
 #include "lp_dense_tile.h"
@@ -19,6 +21,21 @@ namespace mfma {
 namespace {
 
 constexpr int RW = 4;  // waves per workgroup
+
+// sigma (or sigma') of every value with the device library's tanh: the residual
+// measures the solves, whose tanh has an absolute error of a few ulp of 1 (and so a
+// relative one of percents for |z| near 1e-6).
+template <typename V, int NB, int NV, bool DERIV>
+__device__ __forceinline__ void apply_exact(V (&z)[NB], int act) {
+  if (act != ACT_TANH) {
+    apply<V, NB, NV>(z, act, DERIV);
+    return;
+  }
+#pragma unroll
+  for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+    for (int r = 0; r < NV; ++r) z[mb][r] = DERIV ? dact_f<float, ACT_TANH>(z[mb][r]) : act_f<float, ACT_TANH>(z[mb][r]);
+}
 
 // Adjoint, width 64: its rows and column operands are held to three waves per SIMD.
 template <int Q, int DIR>
@@ -64,12 +81,12 @@ void k_resid(ResidArgs a, int ntiles, int run) {
     V s[NB];
     if constexpr (FWD) {
       Lt::template prod<C::LD>(s, x, W[j & 1], lane);
-      apply<V, NB, NV>(s, a.act, false);
+      apply_exact<V, NB, NV, false>(s, a.act);
     } else {
       V d[NB];
       Lt::template prod<C::LD, false>(d, u, W[j & 1], lane);
       Lt::load(u, U + nn * slice + row);
-      apply<V, NB, NV>(d, a.act, true);
+      apply_exact<V, NB, NV, true>(d, a.act);
 #pragma unroll
       for (int mb = 0; mb < NB; ++mb) d[mb] = d[mb] * x[mb];
       Lt::template prod_t<C::LD, false>(s, d, W[j & 1], lane);

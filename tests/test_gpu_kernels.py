@@ -303,6 +303,20 @@ def test_dense_residual_runs(q, N, B):
             assert abs(got - r ** 0.5) <= (q + 8) * EPS["f32"] * scale, (a, which)
 
 
+# the residual's tanh is accurate relative to its value, also near zero: a zero state and
+# zero weights leave r = h tanh(b), whose norm is off by the few ulp of one tanh
+@pytest.mark.parametrize("dtype,q", [("f32", 8), ("f32", 16), ("f32", 32), ("f32", 64), ("f32", 220), ("f64", 16)])
+@pytest.mark.parametrize("size", [1e-6, 1e-3, 0.3])
+def test_residual_of_small_tanh(dtype, q, size):
+    N, B = 3, 50
+    p = L.problem(dtype, "dense", "tanh", N, B, q, h=1.0)
+    K, b = torch.zeros(N, q, q, device="cuda", dtype=DT[dtype]), rnd(1, N, q, dtype=DT[dtype], std=size)
+    U = torch.zeros(N + 1, B, q, device="cuda", dtype=DT[dtype])
+    got = L.lp_residual_norm(p, L.LP_STATE, K, b, U, None, L.alloc_workspace(p))
+    ref = B ** 0.5 * float(torch.tanh(b.double()).norm())
+    assert abs(got - ref) <= 8 * EPS[dtype] * ref
+
+
 # one launch up to 8192 elements, partial sums above: fp64 sums of up to 2^17 products
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("n", [0, 1, 1023, 1025, 8191, 8192, 8193, 131073])
