@@ -251,14 +251,53 @@ __device__ __forceinline__ void publish(bf16x8* sh, const Val<T>& v, const Ctx<Q
   }
 }
 
-// z += K_n v (or K_n^T v) for the published v (sign included). Two panels of weights are in flight;
+constexpr f32x4 ZERO[2] = {f32x4{}, f32x4{}};
+
+// The results that are not finite, again with fp32 instructions (z = init + A v; the
+// weights past the width, which a padded state value of zero does not cancel here when
+// they are not finite, count as zero).
+template <int Q, int T, bool TR>
+__device__ __forceinline__ void prod_again(Val<T>& z, const f32x4 (&init)[2], const float* __restrict__ Kn,
+                                           const bf16x8* B, const Ctx<Q, T>& c) {
+  constexpr int NP = Geo<Q>::NP;
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    f32x4 f[2] = {init[0], init[1]};
+#pragma unroll 1
+    for (int p = 0; p < NP; ++p) {
+      Raw q;
+      fetch_a<Q, TR>(q, Kn, p, c.w, c.lane);
+      Split8 b;
+#pragma unroll
+      for (int part = 0; part < 3; ++part) b.p[part] = B[((t * NP + p) * 3 + part) * 64];
+      const f32x8 x = join8(b);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bool in = 32 * p + 16 * h + 4 * c.g < Q;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+            f[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? q.r[m][h][r] : 0.f, x[4 * h + r], f[m], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) z[t][m] = pick(z[t][m], f[m]);
+  }
+}
+
+// z = init + K_n v (or K_n^T v) for the published v (sign included). Two panels of weights are in flight;
 // q0, q1 hold panels 0 and 1 on entry and those of the next product (Knext, kind
 // NTR; nullptr: none) on return.
 template <int Q, int T, bool TR, bool NTR>
-__device__ __forceinline__ void prod(Val<T>& z, const float* __restrict__ Kn, const bf16x8* sh, const Ctx<Q, T>& c,
-                                     Raw& q0, Raw& q1, const float* __restrict__ Knext) {
+__device__ __forceinline__ void prod(Val<T>& z, const f32x4 (&init)[2], const float* __restrict__ Kn, const bf16x8* sh,
+                                     const Ctx<Q, T>& c, Raw& q0, Raw& q1, const float* __restrict__ Knext) {
   constexpr int NP = Geo<Q>::NP;
   const bf16x8* B = sh + c.lane;
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int m = 0; m < 2; ++m) z[t][m] = init[m];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     Raw& q = p & 1 ? q1 : q0;
@@ -278,6 +317,10 @@ __device__ __forceinline__ void prod(Val<T>& z, const float* __restrict__ Kn, co
     fetch_a<Q, NTR>(q0, Knext, 0, c.w, c.lane);
     fetch_a<Q, NTR>(q1, Knext, 1, c.w, c.lane);
   }
+  f32x4 sum = z[0][0] + z[0][1];
+#pragma unroll
+  for (int t = 1; t < T; ++t) sum += z[t][0] + z[t][1];
+  if (__builtin_expect(!all_finite(sum), 0)) prod_again<Q, T, TR>(z, init, Kn, B, c);
 }
 
 // Work item of linear workgroup id L: the dispatcher deals workgroups to the 8
@@ -348,12 +391,9 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
     const float sgn = sign(j);
     f32x4 b2[2];
     load2(b2, bn, cx.ok1);
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      z[t][0] = sgn * b2[0];
-      z[t][1] = sgn * b2[1];
-    }
-    prod<Q, T, false, false>(z, layer(j), sh, cx, q0, q1, j + 1 < nsteps + (extra ? 1 : 0) ? layer(j + 1) : nullptr);
+    b2[0] *= sgn;
+    b2[1] *= sgn;
+    prod<Q, T, false, false>(z, b2, layer(j), sh, cx, q0, q1, j + 1 < nsteps + (extra ? 1 : 0) ? layer(j + 1) : nullptr);
     scale<T>(z, sgn);
   };
   for (int j = 0; j < nsteps; ++j) {
@@ -455,12 +495,9 @@ __device__ __forceinline__ void publish_s(const Val<T>& v, const SweepArgs& a, s
     __syncthreads();
     f32x4 b2[2];
     load2(b2, static_cast<const float*>(a.b) + n * Q + 32 * cx.w + 4 * cx.g, cx.ok1);
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      d[t][0] = sgn * b2[0];
-      d[t][1] = sgn * b2[1];
-    }
-    prod<Q, T, false, true>(d, Kn, sh, cx, q0, q1, Kn);
+    b2[0] *= sgn;
+    b2[1] *= sgn;
+    prod<Q, T, false, true>(d, b2, Kn, sh, cx, q0, q1, Kn);
     scale<T>(d, sgn);
     apply<true, T>(d, a.act, cx.ok1);
     __syncthreads();
@@ -519,11 +556,9 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
     const size_t n = (size_t)i * a.stride;
     publish_s<Q, REC, T>(v, a, n, slice, sh, cx, q0, q1);
     Val<T> w;
-#pragma unroll
-    for (int t = 0; t < T; ++t) w[t][0] = w[t][1] = 0.f;
     // the next product: the next step's first one, or the coarse step's with the same weights
     const float* next = j + 1 < nsteps ? layer(j + 1) : MODE == SWEEP_FRES ? layer(j) : nullptr;
-    prod<Q, T, true, REC>(w, layer(j), sh, cx, q0, q1, next);
+    prod<Q, T, true, REC>(w, ZERO, layer(j), sh, cx, q0, q1, next);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       if (!cx.ok1) w[t][1] = 0.f;
@@ -571,9 +606,7 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
     load_rows<Q, T>(v, cup, cx);
     publish_s<Q, REC, T>(v, a, n, slice, sh, cx, q0, q1);
     Val<T> w;
-#pragma unroll
-    for (int t = 0; t < T; ++t) w[t][0] = w[t][1] = 0.f;
-    prod<Q, T, true, true>(w, K + n * (Q * Q), sh, cx, q0, q1, nullptr);
+    prod<Q, T, true, true>(w, ZERO, K + n * (Q * Q), sh, cx, q0, q1, nullptr);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       if (!cx.on[t]) continue;
@@ -626,12 +659,9 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
   __syncthreads();
   f32x4 b2[2];
   load2(b2, static_cast<const float*>(a.b) + (size_t)n * Q + 32 * cx.w + 4 * cx.g, cx.ok1);
-#pragma unroll
-  for (int t = 0; t < T; ++t) {
-    z[t][0] = sgn * b2[0];
-    z[t][1] = sgn * b2[1];
-  }
-  prod<Q, T, false, true>(z, Kn, sh, cx, q0, q1, DIR == DIR_ADJ ? Kn : nullptr);
+  b2[0] *= sgn;
+  b2[1] *= sgn;
+  prod<Q, T, false, true>(z, b2, Kn, sh, cx, q0, q1, DIR == DIR_ADJ ? Kn : nullptr);
   scale<T>(z, sgn);
   const float* next = DIR == DIR_FWD ? U + (size_t)(n + 1) * slice : L + (size_t)n * slice;
   if constexpr (DIR == DIR_FWD) {
@@ -646,9 +676,7 @@ __global__ __launch_bounds__(Geo<Q>::NT) __attribute__((amdgpu_waves_per_eu(2, 2
     __syncthreads();
     publish<Q, T>(sh, z, cx, sgn);
     __syncthreads();
-#pragma unroll
-    for (int t = 0; t < T; ++t) z[t][0] = z[t][1] = 0.f;
-    prod<Q, T, true, true>(z, Kn, sh, cx, q0, q1, nullptr);
+    prod<Q, T, true, true>(z, ZERO, Kn, sh, cx, q0, q1, nullptr);
 #pragma unroll
     for (int t = 0; t < T; ++t)
       if (!cx.ok1) z[t][1] = 0.f;
@@ -714,12 +742,9 @@ __global__ __launch_bounds__(Geo<Q>::NT) void k_grad(GradArgs a) {
       __syncthreads();
       f32x4 b2[2];
       load2(b2, static_cast<const float*>(a.b) + (size_t)n * Q + 32 * cx.w + 4 * cx.g, cx.ok1);
-#pragma unroll
-      for (int t = 0; t < GT; ++t) {
-        s[t][0] = sgn * b2[0];
-        s[t][1] = sgn * b2[1];
-      }
-      prod<Q, GT, false, false>(s, Kn, sh, cx, q0, q1, nullptr);
+      b2[0] *= sgn;
+      b2[1] *= sgn;
+      prod<Q, GT, false, false>(s, b2, Kn, sh, cx, q0, q1, nullptr);
       scale<GT>(s, sgn);
       apply<true, GT>(s, a.act, cx.ok1);
     }

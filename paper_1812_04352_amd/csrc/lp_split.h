@@ -9,8 +9,14 @@
 // error against 64 bits is no larger: 0.37e-7, 0.94e-7 and 2.1e-7 relative for
 // contractions of 32, 64 and 224 terms, 1.0e-7, 1.5e-7 and 2.7e-7 with the fp32
 // instruction (one bf16 instruction sums 32 terms at once, the fp32 chain rounds
-// every fourth). The split needs no scaling (bf16 has fp32's exponent range); an
-// infinite or NaN value gives NaN.
+// every fourth). The split needs no scaling (bf16 has fp32's exponent range; below
+// 2^-110 its last part loses bits).
+//
+// An operand that is infinite, or finite but beyond the largest bf16 value, leaves NaN
+// in every result that it takes part in. So a result that is not finite is formed again
+// with fp32 instructions from the joined parts (all_finite, join8, pick): infinities
+// and overflow come out as fp32 gives them, and the finite results of other examples
+// keep their bits.
 //
 // The accumulation rounds towards minus infinity by a small part of its last place
 // (the mean error of sums of positive terms is -0.8e-9, -3.5e-9 and -7.7e-9 for 32, 96
@@ -23,7 +29,9 @@
 // every level and every kernel evaluates a layer the same way bit for bit.
 #pragma once
 
+#include <float.h>
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "lp_layer_sign.h"
@@ -64,6 +72,30 @@ __device__ __forceinline__ Split8 split8(f32x8 x) {
 
 __device__ __forceinline__ Split8 split8(split_f32x4 a, split_f32x4 b) {
   return split8(__builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// The values of a split (what is beyond bf16's range comes back as the largest float).
+__device__ __forceinline__ f32x8 join8(const Split8& s) {
+  f32x8 x;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float a = (float)s.p[0][i], b = (float)s.p[1][i], c = (float)s.p[2][i];
+    x[i] = fabsf(a) < INFINITY ? a + (b + c) : b != b ? a : copysignf(FLT_MAX, a);
+  }
+  return x;
+}
+
+// Whether every value of the wave whose sum a lane passes is finite (a sum that
+// overflows says no, which costs time only).
+__device__ __forceinline__ bool all_finite(split_f32x4 sum) {
+  return !__any(!(fabsf((sum[0] + sum[1]) + (sum[2] + sum[3])) < INFINITY));
+}
+
+// z where it is finite, else f
+__device__ __forceinline__ split_f32x4 pick(split_f32x4 z, split_f32x4 f) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) z[r] = fabsf(z[r]) < INFINITY ? z[r] : f[r];
+  return z;
 }
 
 // The four products of two A and two B fragments, their chains' instructions in turn.

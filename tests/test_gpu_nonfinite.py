@@ -1,0 +1,91 @@
+"""Infinite, NaN and very large operands in the families that run split bf16 products
+(width 220): results as fp32 arithmetic gives them, and the other examples' bits
+untouched. The reference is the definition in 64 bits, rounded to 32 (products beyond
+the range of fp32 become infinite in both)."""
+import pytest
+import torch
+
+from paper_1812_04352_amd import lp as L
+
+pytestmark = pytest.mark.gpu
+INF, BIG = float("inf"), 3.4e38  # BIG is finite in fp32 and beyond the largest bf16 value, 3.39e38
+
+
+def act(z, a):
+    if a == "tanh":
+        return torch.tanh(z)
+    return torch.where(z > 0, z, torch.zeros_like(z)) if a == "relu" else z
+
+
+def dact(z, a):
+    if a == "tanh":
+        return 1.0 - torch.tanh(z) ** 2
+    return (z > 0).to(z.dtype) if a == "relu" else torch.ones_like(z)
+
+
+def f32(x):
+    return x.float().double()
+
+
+def same(got, ref, what):
+    got, ref = got.double().cpu(), f32(ref).cpu()
+    assert torch.equal(got.isnan(), ref.isnan()), what
+    fin = ref.isfinite()
+    assert torch.equal(got[~fin & ~ref.isnan()], ref[~fin & ~ref.isnan()]), what
+    if fin.any():
+        assert float((got[fin] - ref[fin]).abs().max()) <= 1e-5 * float(ref[fin].abs().max()), what
+
+
+def normal(seed, *shape, std=1.0):
+    return torch.randn(*shape, generator=torch.Generator().manual_seed(seed)).mul_(std).cuda()
+
+
+@pytest.mark.parametrize("where", ["state", "weight", "bias"])
+@pytest.mark.parametrize("value", [INF, -INF, BIG, float("nan")])
+@pytest.mark.parametrize("a", ["tanh", "relu", "identity"])
+def test_wide_layers(a, value, where):
+    N, B, q, h = 1, 40, 220, 0.5
+    p = L.problem("f32", "dense", a, N, B, q, h=h)
+    # (small weights beside BIG, so that no sum overflows on the way)
+    K, b = normal(1, N, q, q, std=1e-4 if value == BIG else 0.05), normal(2, N, q, std=0.1)
+    U0, LN = normal(3, B, q), normal(4, B, q)
+    bad = torch.zeros(B, dtype=torch.bool)
+    if where == "state":
+        U0[17, 219] = value
+        LN[21, 3] = value
+        bad[17] = bad[21] = True
+    elif where == "weight":
+        K[0, 33, 0] = value
+        bad[:] = True
+    else:
+        b[0, 7] = value
+        bad[:] = True
+
+    def solve(U0, LN, record):
+        U, Lam = torch.zeros(N + 1, B, q, device="cuda"), torch.zeros(N + 1, B, q, device="cuda")
+        U[0], Lam[N] = U0, LN
+        rec = L.alloc_dsig(p) if record and L.lp_dsig_bytes(p) else None
+        L.lp_serial_forward(p, K, b, U, dsig=rec)
+        L.lp_serial_adjoint(p, K, b, U, Lam, dsig=rec)
+        return U, Lam
+
+    Kd, bd, u, lam = K[0].double().cpu(), b[0].double().cpu(), U0.double().cpu(), LN.double().cpu()
+    z = f32(u @ Kd.T) + bd
+    ref = f32(u + h * act(z, a))
+    s = f32(dact(z, a) * lam)
+    adj = f32(lam + h * f32(s @ Kd))
+    for record in (True, False):
+        U, Lam = solve(U0, LN, record)
+        same(U[1], ref, ("state", record))
+        same(Lam[0], adj, ("adjoint", record))
+        if where == "state":  # the other examples' results are those of a batch without such values
+            Uf, Lf = solve(torch.where(U0.isfinite() & (U0.abs() < 1e38), U0, 0), torch.where(LN.isfinite() & (LN.abs() < 1e38), LN, 0), record)
+            assert torch.equal(U[1][~bad.cuda()], Uf[1][~bad.cuda()])
+            assert torch.equal(Lam[0][~bad.cuda()], Lf[0][~bad.cuda()])
+    # a residual with such a value is reported, not passed over
+    if where == "state" and value != BIG:
+        with pytest.raises(L.LpError) as e:
+            L.lp_residual_norm(p, L.LP_STATE, K, b, solve(U0, LN, False)[0], None, L.alloc_workspace(p))
+        assert e.value.status == L.LP_ENONFINITE
+        with pytest.raises(L.LpError):  # clear the device's flag
+            L.lp_check_finite()
