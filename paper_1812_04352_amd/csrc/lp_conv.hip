@@ -326,6 +326,14 @@ __device__ __forceinline__ f32x4 bias_px(const float* sw, int lane) {
   return f32x4{sw[KW + co], sw[KW + co], sw[KW + co + 1], sw[KW + co + 1]};
 }
 
+// ReLU that passes NaN on. A split product with an operand that is not finite, or beyond
+// the largest bf16 value, is NaN (fp32 instructions give infinities); the activation
+// must not turn that into a 0 that no state or residual shows.
+__device__ __forceinline__ float relu_nan(float z) { return __builtin_elementwise_maximum(z, 0.f); }
+__device__ __forceinline__ float smoothrelu_nan(float z) {
+  return fabsf(z) <= 0.1f ? (2.5f * z + 0.5f) * z + 0.025f : relu_nan(z);
+}
+
 // sigma (D = false) or sigma' (D = true) of the wave's tiles, one branch on the
 // activation for all of them
 template <bool D>
@@ -345,7 +353,7 @@ __device__ __forceinline__ void act_tiles(f32x4 (&z)[TPW], int act) {
 #pragma unroll
       for (int tt = 0; tt < TPW; ++tt) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) z[tt][r] = D ? (z[tt][r] > 0.f ? 1.f : 0.f) : (z[tt][r] > 0.f ? z[tt][r] : 0.f);
+        for (int r = 0; r < 4; ++r) z[tt][r] = D ? (z[tt][r] > 0.f ? 1.f : 0.f) : relu_nan(z[tt][r]);
       }
       break;
     case ACT_SMOOTHRELU:
@@ -353,7 +361,7 @@ __device__ __forceinline__ void act_tiles(f32x4 (&z)[TPW], int act) {
       for (int tt = 0; tt < TPW; ++tt) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          z[tt][r] = D ? dact_f<float, ACT_SMOOTHRELU>(z[tt][r]) : act_f<float, ACT_SMOOTHRELU>(z[tt][r]);
+          z[tt][r] = D ? dact_f<float, ACT_SMOOTHRELU>(z[tt][r]) : smoothrelu_nan(z[tt][r]);
       }
       break;
     default:
@@ -497,7 +505,7 @@ void k_fwd(SweepArgs a, SGeo ga) {
   // weight entries per thread while staging (the specialised geometry fixes the thread count)
   constexpr int WPT = GH ? (WV + 64 * make_geo(GH, GW).NW - 1) / (64 * make_geo(GH, GW).NW) : (WV + 63) / 64;
   const SGeo g = geo_of<GH, GW>(ga);
-  extern __shared__ float lds[];
+  extern __shared__ __align__(16) float lds[];  // (the split image is read 16 bytes at a time)
   char* buf = reinterpret_cast<char*>(lds);  // the split image
   float* sw = lds + 3 * g.PS / 4;            // two layers
   __shared__ double red[MAXW];
@@ -708,7 +716,7 @@ void k_adj(SweepArgs a, SGeo ga) {
   // weight entries per thread while staging (the specialised geometry fixes the thread count)
   constexpr int WPT = GH ? (WV + 64 * make_geo(GH, GW).NW - 1) / (64 * make_geo(GH, GW).NW) : (WV + 63) / 64;
   const SGeo g = geo_of<GH, GW>(ga);
-  extern __shared__ float lds[];
+  extern __shared__ __align__(16) float lds[];
   char* buf = reinterpret_cast<char*>(lds);  // the split image: u, then s
   float* sw = lds + 3 * g.PS / 4;            // two layers
   __shared__ double red[MAXW];
@@ -932,7 +940,7 @@ void k_adj(SweepArgs a, SGeo ga) {
 // example's sum of r^2 (fp64, lanes and waves combined in a fixed order).
 template <int DIR>
 __global__ __launch_bounds__(64 * MAXW) void k_resid(ResidArgs a, SGeo g) {
-  extern __shared__ float lds[];
+  extern __shared__ __align__(16) float lds[];
   char* buf = reinterpret_cast<char*>(lds);  // the split image: U[n], then (adjoint) s
   float* sw = lds + 3 * g.PS / 4;            // the layer's weights
   __shared__ double red[MAXW];
@@ -1022,7 +1030,7 @@ template <int GH, int GW, int RK>
 __global__ __launch_bounds__(64 * MAXW) void k_grad(GradArgs a, SGeo ga) {
   constexpr bool REC = RK != 0, RB = RK == 1;
   const SGeo g = geo_of<GH, GW>(ga);
-  extern __shared__ float lds[];
+  extern __shared__ __align__(16) float lds[];
   float* bu = lds;                   // CH * CS: u
   float* bs = lds + CH * g.CS;       // CH * CS: s
   float* sw = lds + 2 * CH * g.CS;   // the layer's weights

@@ -13,10 +13,12 @@
 // 2^-110 its last part loses bits).
 //
 // An operand that is infinite, or finite but beyond the largest bf16 value, leaves NaN
-// in every result that it takes part in. So a result that is not finite is formed again
-// with fp32 instructions from the joined parts (all_finite, join8, pick): infinities
-// and overflow come out as fp32 gives them, and the finite results of other examples
-// keep their bits.
+// in every result that it takes part in. Width 220 forms results that are not finite
+// again with fp32 instructions from the joined parts (all_finite, join8, pick), which
+// gives infinities and overflow as fp32 has them and leaves the other examples' bits.
+// The convolutions have no registers to spare for that (the check and the second form
+// made the 28 x 28 solves 3 to 7 % slower, other sizes up to 30 %): their activations pass the
+// NaN on, so that state and residual show it.
 //
 // The accumulation rounds towards minus infinity by a small part of its last place
 // (the mean error of sums of positive terms is -0.8e-9, -3.5e-9 and -7.7e-9 for 32, 96

@@ -1,7 +1,7 @@
-"""Infinite, NaN and very large operands in the families that run split bf16 products
-(width 220): results as fp32 arithmetic gives them, and the other examples' bits
+"""Infinite, NaN and very large operands in the families that run split bf16 products.
+Width 220: results as fp32 arithmetic gives them, and the other examples' bits
 untouched. The reference is the definition in 64 bits, rounded to 32 (products beyond
-the range of fp32 become infinite in both)."""
+the range of fp32 become infinite in both). 3x3 convolutions: NaN, which nothing swallows."""
 import pytest
 import torch
 
@@ -29,9 +29,9 @@ def f32(x):
 
 def same(got, ref, what):
     got, ref = got.double().cpu(), f32(ref).cpu()
-    assert torch.equal(got.isnan(), ref.isnan()), what
+    assert bool((got.isnan() == ref.isnan()).all()), what
     fin = ref.isfinite()
-    assert torch.equal(got[~fin & ~ref.isnan()], ref[~fin & ~ref.isnan()]), what
+    assert bool((got[ref.isinf()] == ref[ref.isinf()]).all()), what
     if fin.any():
         assert float((got[fin] - ref[fin]).abs().max()) <= 1e-5 * float(ref[fin].abs().max()), what
 
@@ -89,3 +89,53 @@ def test_wide_layers(a, value, where):
         assert e.value.status == L.LP_ENONFINITE
         with pytest.raises(L.LpError):  # clear the device's flag
             L.lp_check_finite()
+
+
+# A split product with an operand that is not finite, or beyond the largest bf16 value, is
+# NaN, and the state shows it with every activation (also ReLU, which gives 0 for NaN by
+# comparison): the residual reports it. The image's own pixels beside it, and the other
+# images' bits, are untouched.
+@pytest.mark.parametrize("where", ["state", "weight"])
+@pytest.mark.parametrize("value", [INF, -INF, BIG, float("nan")])
+@pytest.mark.parametrize("a", ["tanh", "relu", "smoothrelu", "identity"])
+@pytest.mark.parametrize("H,W", [(28, 28), (12, 13)])
+def test_conv_layers(H, W, a, value, where):
+    N, B, C = 1, 5, 8
+    p = L.problem("f32", "conv3x3", a, N, B, C, H, W, h=0.5)
+    K, b = normal(1, N, C, C, 3, 3, std=0.1), normal(2, N, C, std=0.1)
+    U0, LN = normal(3, B, C, H, W), normal(4, B, C, H, W)
+    U0f, LNf = U0.clone(), LN.clone()
+    y, x = H // 2, W // 2
+    if where == "state":
+        U0[1, 5, y, x] = value
+        LN[3, :, y, x] = value  # (in every channel: sigma' may be zero in some)
+    else:
+        K[0, 6, 1, 1, 1] = value
+
+    def solve(U0, LN, record):
+        U, Lam = torch.zeros(N + 1, B, C, H, W, device="cuda"), torch.zeros(N + 1, B, C, H, W, device="cuda")
+        U[0], Lam[N] = U0, LN
+        rec = L.alloc_dsig(p) if record and L.lp_dsig_bytes(p) else None
+        L.lp_serial_forward(p, K, b, U, dsig=rec)
+        L.lp_serial_adjoint(p, K, b, U, Lam, dsig=rec)
+        return U, Lam
+
+    ws = L.alloc_workspace(p)
+    for record in (True, False):
+        U, Lam = solve(U0, LN, record)
+        if where == "state":  # the 3 x 3 pixels around it, all channels; and no pixel four rows or two columns away
+            assert not U[1, 1, :, y - 1:y + 2, x - 1:x + 2].isfinite().any()
+            assert U[1, 1, :, :y - 4].isfinite().all() and U[1, 1, :, :, x + 2:].isfinite().all()
+            assert value == BIG or not Lam[0, 3, :, y, x].isfinite().any()
+            Uf, Lf = solve(U0f, LNf, record)
+            for got, ref, others in ((U[1], Uf[1], [0, 2, 3, 4]), (Lam[0], Lf[0], [0, 2, 4])):
+                assert torch.equal(got[others], ref[others])
+        else:  # the channel that the weight feeds
+            assert not U[1, :, 6].isfinite().any() and U[1, :, [0, 1, 2, 3, 4, 5, 7]].isfinite().all()
+            assert value == BIG or not Lam[0, :, 1].isfinite().all()
+        for which in (L.LP_STATE, L.LP_ADJOINT)[:1 if value == BIG else 2]:  # (sigma' times BIG may be in range)
+            with pytest.raises(L.LpError) as e:
+                L.lp_residual_norm(p, which, K, b, U, Lam, ws)
+            assert e.value.status == L.LP_ENONFINITE
+    with pytest.raises(L.LpError):  # clear the device's flag
+        L.lp_check_finite()
