@@ -30,11 +30,12 @@
  *                          (conv: [N][C][C][3][3], K[n][co][ci][ty][tx])
  *       bias b             [N][q]          (conv: [N][C])
  *   - U and Lam must not alias each other or the workspace.
- *   - Not-a-number and infinite values pass through the layers as the arithmetic
- *     of the dtype has them and end in a non-finite residual norm. In 3x3
- *     convolutions an operand that is infinite, or above 3.39e38 in magnitude,
- *     gives NaN in the pre-activations that it enters, and every activation
- *     passes NaN on.
+ *   - Arrays of floating-point values need no more than their element's alignment
+ *     (weights may be views into a flat parameter vector); ws 256 bytes and dsig
+ *     16 bytes.
+ *   - In 3x3 convolutions an operand that is infinite, or above 3.39e38 in
+ *     magnitude, gives NaN in the pre-activations that it enters, and the
+ *     activations pass NaN on to the state (in dense layers ReLU of NaN is 0).
  *   - Calls are re-entrant when given distinct workspaces and outputs.
  *   - Error behaviour: an argument check failing returns LP_EINVAL (or
  *     LP_EUNSUPPORTED for a valid but unimplemented combination) before any work

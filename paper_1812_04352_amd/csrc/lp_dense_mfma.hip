@@ -327,7 +327,7 @@ __device__ __forceinline__ void wall_fetch(WAll<Q, NL, WAVES>& r, const float* _
     const int idx = threadIdx.x + p * A::NT;
     if (idx < NL * A::KV) {
       const int j = idx / A::KV, w = idx - j * A::KV;
-      r.k[p] = reinterpret_cast<const f32x4*>(K + (size_t)((n0 + dn * j) * stride) * (Q * Q))[w];
+      r.k[p] = reinterpret_cast<const f32x4g*>(K + (size_t)((n0 + dn * j) * stride) * (Q * Q))[w];
     }
   }
 #pragma unroll
@@ -335,7 +335,7 @@ __device__ __forceinline__ void wall_fetch(WAll<Q, NL, WAVES>& r, const float* _
     const int idx = threadIdx.x + p * A::NT;
     if (idx < NL * A::BV) {
       const int j = idx / A::BV, w = idx - j * A::BV;
-      r.b[p] = reinterpret_cast<const f32x4*>(b + (size_t)((n0 + dn * j) * stride) * Q)[w];
+      r.b[p] = reinterpret_cast<const f32x4g*>(b + (size_t)((n0 + dn * j) * stride) * Q)[w];
     }
   }
 }

@@ -40,9 +40,9 @@ struct FwdOps {
     const float* bn = bb + n * (size_t)Q + 4 * g;
 #pragma unroll
     for (int ob = 0; ob < NB; ++ob) {
-      b[ob] = *reinterpret_cast<const f32x4*>(bn + 16 * ob);
+      b[ob] = *reinterpret_cast<const f32x4g*>(bn + 16 * ob);
 #pragma unroll
-      for (int ib = 0; ib < NB; ++ib) a[ob][ib] = *reinterpret_cast<const f32x4*>(Kn + 16 * ob * Q + 16 * ib);
+      for (int ib = 0; ib < NB; ++ib) a[ob][ib] = *reinterpret_cast<const f32x4g*>(Kn + 16 * ob * Q + 16 * ib);
     }
   }
   // the blocks' chains of instructions in turn

@@ -32,6 +32,9 @@ struct Cfg {
 };
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// four floats in global memory: the caller's arrays may be views into a flat vector, with
+// no more than their element's alignment
+typedef float f32x4g __attribute__((ext_vector_type(4), aligned(4)));
 
 // One layer's weights in flight between global memory and LDS.
 template <int Q, int WAVES>
@@ -44,13 +47,13 @@ template <int Q, int WAVES>
 __device__ __forceinline__ void w_fetch(WRegs<Q, WAVES>& r, const float* __restrict__ K,
                                         const float* __restrict__ b, size_t n) {
   using C = Cfg<Q, WAVES>;
-  const f32x4* Kn = reinterpret_cast<const f32x4*>(K + n * (size_t)(Q * Q));
+  const f32x4g* Kn = reinterpret_cast<const f32x4g*>(K + n * (size_t)(Q * Q));
 #pragma unroll
   for (int p = 0; p < C::PK; ++p) {
     const int idx = threadIdx.x + p * C::NT;
-    r.k[p] = (!C::PART || idx < Q * Q / 4) ? Kn[idx] : f32x4{};
+    r.k[p] = (!C::PART || idx < Q * Q / 4) ? (f32x4)Kn[idx] : f32x4{};
   }
-  r.b = threadIdx.x < Q / 4 ? reinterpret_cast<const f32x4*>(b + n * (size_t)Q)[threadIdx.x] : f32x4{};
+  r.b = threadIdx.x < Q / 4 ? (f32x4)reinterpret_cast<const f32x4g*>(b + n * (size_t)Q)[threadIdx.x] : f32x4{};
 }
 
 template <int Q, int WAVES>
@@ -124,7 +127,7 @@ struct Lay<Q, 32> {
     for (int mb = 0; mb < NB; ++mb)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const f32x4 x = *reinterpret_cast<const f32x4*>(p + 32 * mb + 8 * g);
+        const f32x4 x = *reinterpret_cast<const f32x4g*>(p + 32 * mb + 8 * g);
 #pragma unroll
         for (int t = 0; t < 4; ++t) v[mb][4 * g + t] = x[t];
       }
@@ -135,7 +138,7 @@ struct Lay<Q, 32> {
     for (int mb = 0; mb < NB; ++mb)
 #pragma unroll
       for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<f32x4*>(p + 32 * mb + 8 * g) =
+        *reinterpret_cast<f32x4g*>(p + 32 * mb + 8 * g) =
             f32x4{v[mb][4 * g + 0], v[mb][4 * g + 1], v[mb][4 * g + 2], v[mb][4 * g + 3]};
   }
 
@@ -210,12 +213,12 @@ struct Lay<Q, 16> {
   // p points at the example's row + 4*(lane/16)
   __device__ static void load(V (&v)[NB], const float* __restrict__ p) {
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) v[mb] = *reinterpret_cast<const f32x4*>(p + 16 * mb);
+    for (int mb = 0; mb < NB; ++mb) v[mb] = *reinterpret_cast<const f32x4g*>(p + 16 * mb);
   }
 
   __device__ static void store(float* __restrict__ p, const V (&v)[NB]) {
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) *reinterpret_cast<f32x4*>(p + 16 * mb) = v[mb];
+    for (int mb = 0; mb < NB; ++mb) *reinterpret_cast<f32x4g*>(p + 16 * mb) = v[mb];
   }
 
   // sigma' record of ReLU (bits, MaskWord), off at the lane's element offset

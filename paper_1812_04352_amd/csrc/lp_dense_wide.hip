@@ -46,6 +46,9 @@ namespace lp {
 namespace wide {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// four floats in global memory, with their element's alignment (the caller's arrays may
+// be views into a flat vector)
+typedef float f32x4g __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int MODE_SERIAL = 3;
@@ -87,12 +90,12 @@ using Val = f32x4[T][2];  // a wave's values of its T tiles
 
 // one tile's two blocks at p (the lane's element of the example's row)
 __device__ __forceinline__ void load2(f32x4 (&v)[2], const float* __restrict__ p, bool ok1) {
-  v[0] = *reinterpret_cast<const f32x4*>(p);
-  v[1] = ok1 ? *reinterpret_cast<const f32x4*>(p + 16) : f32x4{};
+  v[0] = *reinterpret_cast<const f32x4g*>(p);
+  v[1] = ok1 ? (f32x4)*reinterpret_cast<const f32x4g*>(p + 16) : f32x4{};
 }
 __device__ __forceinline__ void store2(float* __restrict__ p, const f32x4 (&v)[2], bool ok1) {
-  *reinterpret_cast<f32x4*>(p) = v[0];
-  if (ok1) *reinterpret_cast<f32x4*>(p + 16) = v[1];
+  *reinterpret_cast<f32x4g*>(p) = v[0];
+  if (ok1) *reinterpret_cast<f32x4g*>(p + 16) = v[1];
 }
 
 // all tiles, from the row block at base; lanes past the batch read example 0's row
@@ -230,7 +233,7 @@ __device__ __forceinline__ void fetch_a(Raw& a, const float* __restrict__ Kn, in
       if (32 * (p + 1) > Q) k = 32 * p + k < Q ? k : 0;
       const uint32_t off = 4u * (uint32_t)(TR ? k * Q + oc : oc * Q + k);
       if constexpr (!TR) {
-        a.r[m][h] = *reinterpret_cast<const f32x4*>(base + off);
+        a.r[m][h] = *reinterpret_cast<const f32x4g*>(base + off);
       } else {
 #pragma unroll
         for (int t = 0; t < 4; ++t) a.r[m][h][t] = *reinterpret_cast<const float*>(base + t * 4 * Q + off);

@@ -207,7 +207,6 @@ def test_narrow_two_tiles_per_wave(dtype, q):
 def test_wide_tiles_per_workgroup(act_name, record):
     N, B, q, h = 1024, 200, 220, 0.005
     _, K, b, U, Lam = dense_problem("f32", q, act_name, N, B, h=h)
-    K = K.clone()  # 16-byte rows, as every fp32 family of width 32 and up needs
     mg = L.mgrit(cf=4, max_levels=3, max_iter=1)
 
     def solve(U0, LN):
@@ -219,7 +218,6 @@ def test_wide_tiles_per_workgroup(act_name, record):
         L.lp_mgrit_adjoint(p, mg, K, b, u, lam, ws, dsig=rec)
         return u, lam
 
-    b = b.clone()
     u, lam = solve(U[0], Lam[N])
     assert bool(torch.isfinite(u).all()) and bool(torch.isfinite(lam).all())
     for part in (slice(0, 37), slice(185, 200)):
@@ -232,7 +230,6 @@ def test_wide_layers(B):
     N, q, h = 4, 220, 0.05
     for a in ("tanh", "smoothrelu", "identity"):
         p, K, b, U, Lam = dense_problem("f32", q, a, N, B)
-        K, b = K.clone(), b.clone()
         ref = serial_reference(K, b, U, Lam, a, h)
         for record in (True, False):
             rec = L.alloc_dsig(p) if record else None
