@@ -23,10 +23,9 @@ namespace {
 constexpr int MODE_SERIAL = 3;  // SweepArgs.mode of a whole-level serial solve
 
 // Steps in flight: four at width 32. At width 64 a layer's operands take 80
-// registers per lane forward and 64 transposed: two layers, or one where a step needs
-// both (its 128 matrix instructions cover the latency).
-template <int Q, bool BOTH>
-constexpr int SER_D = Q <= 32 ? 4 : BOTH ? 1 : 2;
+// registers per lane forward and 64 transposed: two layers.
+template <int Q>
+constexpr int SER_D = Q <= 32 ? 4 : 2;
 
 // Operands of z = K_n v + b_n, as Lay<Q, 16>::prod reads them from LDS: lane
 // l = 16 g + i has K[16 ob + i][16 ib + 4 g ..] and b[16 ob + 4 g ..].
@@ -92,10 +91,10 @@ struct AdjOps {
 // (Two waves per SIMD are asked for where 256 registers suffice: the compiler then
 // keeps the accumulators out of the accumulation registers.)
 template <int Q, bool REC>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Q == 64 && REC ? 1 : 2, 8))) void k_ser_fwd(SweepArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_ser_fwd(SweepArgs a) {
   using Lt = Lay<Q, 16>;
   using V = typename Lt::V;
-  constexpr int NB = Lt::NB, NV = Lt::NV, D = SER_D<Q, false>;
+  constexpr int NB = Lt::NB, NV = Lt::NV, D = SER_D<Q>;
   const int lane = threadIdx.x & 63;
   const int e = blockIdx.x * 16 + (lane & 15);
   const bool on = e < a.B;
@@ -156,7 +155,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RK == 0 ? 1 
   using Lt = Lay<Q, 16>;
   using V = typename Lt::V;
   constexpr bool REC = RK != 0;
-  constexpr int NB = Lt::NB, NV = Lt::NV, D = SER_D<Q, !REC>;
+  constexpr int NB = Lt::NB, NV = Lt::NV, D = SER_D<Q>;
   const int lane = threadIdx.x & 63;
   const int e = blockIdx.x * 16 + (lane & 15);
   const bool on = e < a.B;
@@ -234,7 +233,7 @@ __global__ __launch_bounds__(64) void k_ser_fwd_lds(SweepArgs a) {
   using C = Cfg<Q, 1>;
   using Lt = Lay<Q, 16>;
   using V = typename Lt::V;
-  constexpr int NB = Lt::NB, NV = Lt::NV, D = SER_D<Q, false>;
+  constexpr int NB = Lt::NB, NV = Lt::NV, D = SER_D<Q>;
   __shared__ float W[2][C::WSZ];
   const int lane = threadIdx.x & 63;
   const int e = blockIdx.x * 16 + (lane & 15);
@@ -304,7 +303,7 @@ __global__ __launch_bounds__(64) void k_ser_adj_lds(SweepArgs a) {
   using C = Cfg<Q, 1>;
   using Lt = Lay<Q, 16>;
   using V = typename Lt::V;
-  constexpr int NB = Lt::NB, NV = Lt::NV, D = SER_D<Q, false>;
+  constexpr int NB = Lt::NB, NV = Lt::NV, D = SER_D<Q>;
   constexpr bool REC = RK != 0;
   __shared__ float W[2][C::WSZ];
   const int lane = threadIdx.x & 63;
@@ -398,27 +397,44 @@ hipError_t serial(int dir, const SerialArgs& s, hipStream_t st) {
   a.dsig = s.dsig;
   a.ustride = s.ustride;
   const dim3 grid((s.B + 15) / 16, 1);
-  // Direct loads up to one wave per CU at width 64 and two at width 32. Forward, 256
-  // layers, direct / through LDS: width 64, 4096 examples 383 / 459 us, 16384 examples
-  // 690 / 543; width 32, 8192 examples 144 / 180, 16384 examples 255 / 227.
-  if (s.B > (Q == 64 ? 4096 : 8192)) {
-    if (dir == DIR_FWD) {
-      if (s.dsig) launch(k_ser_fwd_lds<Q, true>, grid, 64, 0, st, a);
-      else launch(k_ser_fwd_lds<Q, false>, grid, 64, 0, st, a);
-    } else {
-      if (!s.dsig) launch(k_ser_adj_lds<Q, 0>, grid, 64, 0, st, a);
-      else if (s.act == ACT_RELU) launch(k_ser_adj_lds<Q, 1>, grid, 64, 0, st, a);
-      else launch(k_ser_adj_lds<Q, 2>, grid, 64, 0, st, a);
-    }
-    return hipGetLastError();
-  }
+  // Direct loads up to one wave per CU at width 64 and two at width 32, and at width 64 not
+  // where a step needs more registers than they leave (a recorded forward step, an adjoint
+  // step with both products). 128 layers, us, direct / through LDS, ReLU:
+  //   width 32, 500 and 8192 examples: forward 56 / 75 and 67 / 85, with record 94 / 113
+  //     and 99 / 120, adjoint with record 67 / 79 and 73 / 87, without 108 / 116 and
+  //     114 / 121; 256 layers, 16384 examples: forward 255 / 227
+  //   width 64, 500 and 4096 examples: forward 176 / 192 and 185 / 201, adjoint with record
+  //     188 / 214 and 193 / 220; not chosen: forward with record 256 / 245 and 259 / 253,
+  //     adjoint without 328 / 321 and 330 / 325; 256 layers, 16384 examples: forward 690 / 543
+  const bool direct = s.B <= (Q == 64 ? 4096 : 8192);
   if (dir == DIR_FWD) {
-    if (s.dsig) launch(k_ser_fwd<Q, true>, grid, 64, 0, st, a);
-    else launch(k_ser_fwd<Q, false>, grid, 64, 0, st, a);
+    if (s.dsig) {
+      if constexpr (Q != 64) {
+        if (direct) {
+          launch(k_ser_fwd<Q, true>, grid, 64, 0, st, a);
+          return hipGetLastError();
+        }
+      }
+      launch(k_ser_fwd_lds<Q, true>, grid, 64, 0, st, a);
+    } else if (direct) {
+      launch(k_ser_fwd<Q, false>, grid, 64, 0, st, a);
+    } else {
+      launch(k_ser_fwd_lds<Q, false>, grid, 64, 0, st, a);
+    }
+  } else if (!s.dsig) {
+    if constexpr (Q != 64) {
+      if (direct) {
+        launch(k_ser_adj<Q, 0>, grid, 64, 0, st, a);
+        return hipGetLastError();
+      }
+    }
+    launch(k_ser_adj_lds<Q, 0>, grid, 64, 0, st, a);
+  } else if (s.act == ACT_RELU) {
+    if (direct) launch(k_ser_adj<Q, 1>, grid, 64, 0, st, a);
+    else launch(k_ser_adj_lds<Q, 1>, grid, 64, 0, st, a);
   } else {
-    if (!s.dsig) launch(k_ser_adj<Q, 0>, grid, 64, 0, st, a);
-    else if (s.act == ACT_RELU) launch(k_ser_adj<Q, 1>, grid, 64, 0, st, a);
-    else launch(k_ser_adj<Q, 2>, grid, 64, 0, st, a);
+    if (direct) launch(k_ser_adj<Q, 2>, grid, 64, 0, st, a);
+    else launch(k_ser_adj_lds<Q, 2>, grid, 64, 0, st, a);
   }
   return hipGetLastError();
 }

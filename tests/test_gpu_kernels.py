@@ -50,13 +50,15 @@ def within(got, ref, scale, bound, what):
     assert worst <= bound, f"{what}: {worst:.3e} of the absolute sum, bound {bound:.3e}"
 
 
-# tiles of 32 x 32 with 512-byte pieces of the features (forward); tiles of 4 .. 128
-# examples by feature count and 1024 threads (gradient)
+# tiles of 32 x 32 with 512-byte pieces of the features (forward); an example per thread up
+# to 8 features, else 1 to 16 features per lane and 8 or 16 waves (gradient)
 @pytest.mark.parametrize("dtype,act_name,B,q,nf", [
     ("f32", "tanh", 1, 8, 1), ("f32", "relu", 31, 16, 2), ("f32", "smoothrelu", 33, 32, 127), ("f32", "tanh", 129, 32, 128),
     ("f32", "identity", 100, 64, 129), ("f32", "tanh", 257, 220, 220), ("f32", "tanh", 70, 8, 513),
     ("f32", "tanh", 37, 8, 1023), ("f32", "relu", 1500, 32, 1024),
     ("f64", "tanh", 1, 8, 1), ("f64", "smoothrelu", 65, 16, 63), ("f64", "tanh", 257, 32, 65), ("f64", "tanh", 33, 8, 1024),
+    ("f64", "tanh", 5000, 8, 2), ("f64", "smoothrelu", 4097, 16, 3), ("f32", "relu", 4096, 8, 8), ("f32", "tanh", 1025, 16, 9),
+    ("f64", "tanh", 130, 16, 128), ("f64", "tanh", 129, 16, 200), ("f64", "smoothrelu", 100, 8, 513),
 ])
 def test_dense_opening(dtype, act_name, B, q, nf):
     p = L.problem(dtype, "dense", act_name, 1, B, q)
@@ -338,6 +340,14 @@ def test_dense_serial_depths(q, N, batches):
             L.lp_serial_forward(p, K, b, U)
             L.lp_serial_adjoint(p, K, b, U, Lam)
             ref = serial_reference(K, b, U, Lam, a, 0.05)
+            rec = L.alloc_dsig(p) if L.lp_dsig_bytes(p) else None
+            if rec is not None:  # other kernels by the same rule: the same states, the adjoint to rounding
+                V, M = U.clone(), Lam.clone()
+                V[1:] = M[:-1] = float("nan")
+                L.lp_serial_forward(p, K, b, V, dsig=rec)
+                L.lp_serial_adjoint(p, K, b, V, M, dsig=rec)
+                assert torch.equal(V, U)
+                assert float((M.double() - ref[1]).norm() / ref[1].norm()) <= 16 * N * (q + 8) * EPS["f32"], (a, B)
             for got, r in ((U, ref[0]), (Lam, ref[1])):
                 e = float((got.double() - r).norm() / r.norm())
                 assert e <= 16 * N * (q + 8) * EPS["f32"], (a, B, e)
