@@ -302,6 +302,27 @@ def test_dense_residual_runs(q, N, B):
             assert abs(got - r ** 0.5) <= (q + 8) * EPS["f32"] * scale, (a, which)
 
 
+# narrow widths: a wave takes 1 to 16 tiles of 16 examples (by N ceil(B/64) / 8192), the last
+# run being ragged; the bound is that of the runs of layers above
+@pytest.mark.parametrize("dtype,q", NARROW)
+@pytest.mark.parametrize("N,B", [(1024, 1037), (64, 20011), (3, 190001)])
+def test_narrow_residual_runs(dtype, q, N, B):
+    for a in ("tanh", "smoothrelu"):
+        p, K, b, _, _ = dense_problem(dtype, q, a, N, 1, h=0.05)
+        p = L.problem(dtype, "dense", a, N, B, q, h=0.05)
+        V, M = (rnd(k, N + 1, B, q, dtype=DT[dtype]) for k in (7, 8))
+        ws, rs, ra = L.alloc_workspace(p), 0.0, 0.0
+        for n in range(N):
+            u, k, lam = V[n].double(), K[n].double(), M[n + 1].double()
+            z = u @ k.T.contiguous() + b[n].double()
+            rs += float((u + 0.05 * act(z, a) - V[n + 1].double()).square().sum())
+            ra += float((lam + 0.05 * (dact(z, a) * lam) @ k - M[n].double()).square().sum())
+        scale = float(V.double().norm() + M.double().norm())
+        for which, r in ((L.LP_STATE, rs), (L.LP_ADJOINT, ra)):
+            got = L.lp_residual_norm(p, which, K, b, V, M, ws)
+            assert abs(got - r ** 0.5) <= (q + 8) * EPS[dtype] * scale, (a, which)
+
+
 # the residual's tanh is accurate relative to its value, also near zero: a zero state and
 # zero weights leave r = h tanh(b), whose norm is off by the few ulp of one tanh
 @pytest.mark.parametrize("dtype,q", [("f32", 8), ("f32", 16), ("f32", 32), ("f32", 64), ("f32", 220), ("f64", 16)])
