@@ -6,11 +6,11 @@
 // (the dropped ones are at most 2^-25 of |x y| and of either sign). Six
 // v_mfma_f32_16x16x32_bf16 replace eight v_mfma_f32_16x16x4_f32 of twice the time
 // each: measured issue rates 2026 and 138 TFLOP/s, so 2.4 times the fp32 rate. The
-// error against 64 bits is no larger: 0.37e-7, 0.94e-7 and 2.1e-7 relative for
-// contractions of 32, 64 and 224 terms, 1.0e-7, 1.5e-7 and 2.7e-7 with the fp32
-// instruction (one bf16 instruction sums 32 terms at once, the fp32 chain rounds
-// every fourth). The split needs no scaling (bf16 has fp32's exponent range; below
-// 2^-110 its last part loses bits).
+// error against 64 bits is smaller: 0.37e-7, 0.94e-7 and 2.2e-7 relative for
+// contractions of 32, 64 and 220 terms, 1.0e-7, 1.5e-7 and 2.7e-7 with the fp32
+// instruction, which rounds with every product (one bf16 instruction sums 32 terms at
+// once); 3x3 convolutions of 8 channels 0.54e-7 and 1.5e-7. The split needs no scaling
+// (bf16 has fp32's exponent range; below 2^-110 its last part loses bits).
 //
 // An operand that is infinite, or finite but beyond the largest bf16 value, leaves NaN
 // in every result that it takes part in. Width 220 forms results that are not finite
