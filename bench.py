@@ -186,11 +186,11 @@ def kernel_model(wl, kind: str, fwd_iters: int, adj_iters: int, rec: int = 0, cp
 
 # Source files that define each kernel family (besides the shared headers).
 _FAMILY_SOURCES = {
-    "lp::conv::": ["lp_conv.hip"],
-    "lp::mfma::": ["lp_dense_mfma.hip", "lp_dense_tile.h"],
+    "lp::conv::": ["lp_conv.hip", "lp_split.h", "lp_layer_sign.h"],
+    "lp::mfma::": ["lp_dense_mfma.hip", "lp_dense_resid.hip", "lp_dense_serial.hip", "lp_dense_tile.h"],
     "lp::dense::": ["lp_dense_impl.h", "lp_dense_f32.hip"],
     "lp::narrow::": ["lp_dense_narrow.hip"],
-    "lp::wide::": ["lp_dense_wide.hip"],
+    "lp::wide::": ["lp_dense_wide.hip", "lp_split.h", "lp_layer_sign.h"],
 }
 _SHARED_SOURCES = ["lp_internal.h", "lp_device.h"]
 

@@ -18,9 +18,10 @@
 // bytes, one conflict-free write and, for the readers, one conflict-free read per
 // lane, with a barrier before and after. A fragment read feeds 12 matrix
 // instructions, a weight fragment 6 T; the waves run a whole layer between barriers.
-// Padding features (220..223) are never loaded or stored, their weights are zero,
-// and the padded values of every new state are reset to zero after the activation
-// (sigma(0) is not zero for the smoothed ReLU).
+// Padding features (220..223) are never loaded or stored. The weights of a padded
+// contraction index are those of a valid one (fetch_a) and meet padded state values of
+// zero; the results of a padded row are discarded: the padded values of every new state
+// are reset to zero after the activation (sigma(0) is not zero for the smoothed ReLU).
 //
 // T = 6 takes 126 kB of LDS, one workgroup per CU, two waves per SIMD on three SIMDs
 // and one on the fourth; sweeps with fewer workgroups than CUs take T = 4 or 2.

@@ -169,8 +169,8 @@ hipError_t mfma_expand(int q, int act, const void* K, const void* b, const void*
 hipError_t mfma_grad_partials(int q, const GradArgs& a, long nl, hipStream_t st);
 hipError_t mfma_grad_finish(int q, const GradArgs& a, hipStream_t st);
 
-// Dense fp32 matrix-core family for wide layers (lp_dense_wide.hip), width 220:
-// the layer weights stream through LDS in panels
+// Dense fp32 matrix-core family for wide layers (lp_dense_wide.hip), width 220: split
+// bf16 products, the weights from L2 straight to registers
 bool wide_width_supported(int q);
 hipError_t wide_sweep(int q, int dir, const SweepArgs& a, hipStream_t st, int* partials);
 hipError_t wide_serial(int q, int dir, const SerialArgs& a, hipStream_t st);
