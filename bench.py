@@ -229,12 +229,13 @@ def kernel_kind(name: str):
     import re
     if "k_grad<" in name or "k_grad_partial<" in name:
         return "gradient"
-    m = re.search(r"lp::(mfma|conv|dense|narrow|wide)::k_(fwd|adj)(_sweep|_serial|_iv)?<([^>]*)>", name)
+    m = re.search(r"lp::(mfma|conv|dense|narrow|wide)::k_(ser_)?(fwd|adj)(_sweep|_serial|_iv|_lds)?<([^>]*)>",
+                  name)
     if not m:
         return None
-    fam, d, suffix, targs = m.groups()
+    fam, ser, d, suffix, targs = m.groups()
     args = [t.strip() for t in targs.split(",")]
-    if suffix == "_serial":
+    if ser or suffix == "_serial":
         mode = 3
     else:
         mode = int(args[{"mfma": 1, "conv": 0, "dense": 2, "narrow": 2, "wide": 1}[fam]])

@@ -14,6 +14,9 @@ def test_kernel_kind_parses_every_family():
     assert kk("void lp::mfma::k_fwd<32, 3, 1, 16, false>(lp::SweepArgs)") == "fwd_coarsest"
     assert kk("void lp::mfma::k_adj_iv<32, 2, 4, true, true, false>(lp::SweepArgs)") == "adj_corrf"
     assert kk("void lp::mfma::k_fwd_iv<64, 1, 4, false, true>(lp::SweepArgs)") == "fwd_fres"
+    # the serial kernels of widths 32 and 64 are the coarsest kind
+    assert kk("void lp::mfma::k_ser_fwd<32, false>(lp::SerialArgs)") == "fwd_coarsest"
+    assert kk("void lp::mfma::k_ser_adj_lds<64, 16, true>(lp::SerialArgs)") == "adj_coarsest"
     # vector-ALU kernels: mode is the 3rd argument; the serial kernels are the coarsest kind
     assert kk("void lp::dense::k_adj_sweep<double, 8, 1>(lp::SweepArgs)") == "adj_fres"
     assert kk("void lp::dense::k_fwd_serial<double, 8>(lp::SerialArgs)") == "fwd_coarsest"
