@@ -30,7 +30,7 @@
 // sweeps of 1000 examples and 1024 layers, us: forward FC 1106 (panels, fp32
 // instructions), 840 (panels, split products), 725 (this form); forward FRES 1133,
 // 890, 780; adjoint FC 1097, 835, 815; adjoint FRES 1433, 1480, 1020. The matrix
-// pipes are busy 34 to 39 % of the time in these: a layer's activations, splits and
+// pipes are busy 31 to 36 % of the time in these: a layer's activations, splits and
 // barriers come at the same time for all waves, and one workgroup fills the CU.
 // (Reading fragments and splitting weights a pair of tiles ahead was not faster: its
 // registers spill.)
