@@ -5,6 +5,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <limits>
 #include <type_traits>
 
 #include "lp_device.h"
@@ -178,16 +179,19 @@ __global__ __launch_bounds__(NT) void k_open_conv(const T* y, const T* L, T* u0,
   }
 }
 
-// dL[r][f] = sum_e sigma'(z_er) lam0[e][r] y[e][f]; one workgroup of 16 waves per
-// row r (there is no workspace to combine several in). Lane l of a wave holds the
+// dL[r][f] = sum_e sigma'(z_er) lam0[e][r] y[e][f]; one workgroup of 8 or 16 waves
+// per row r (there is no workspace to combine several in). Lane l of a wave holds the
 // features l, l + 64, ... of GE examples at a time, read once, coalesced, straight
 // into registers, the next GE requested before the current ones are used; the
 // waves run without barriers. The GE values of z are added over the lanes in one
 // butterfly that halves their number per exchange, so that sigma' runs once for
 // all of them, and come back as scalars. fp32 sums over GE examples, then fp64 in
-// a fixed order. Bound by the one CU's reads of y: 16384 x 128 fp32, 32 rows:
-// 1776 us with a barrier and a chain of loads per 256 examples, 340 us
-// now.
+// a fixed order. ReLU's decision has to be that of the opening layer, which sums z
+// feature by feature: where the two orders could fall on either side of zero (|z| below
+// about nf / 2 eps sum |L y|: in fp32 one example in 20000 of 64 features, one in 1000
+// of 1024), z is summed again in its order, from scalar loads. 16384 examples, 32 rows,
+// fp32, us: 128 features tanh 1776 with a barrier and a chain of loads per 256
+// examples, 156 now, ReLU 1497 and 176; 1024 features ReLU 9937 and 1091.
 constexpr int GNT = 1024;
 
 template <typename T>
@@ -207,7 +211,7 @@ template <typename T, int ACT, int FPL, int GE, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void k_open_grad_dense(const T* y, const T* L, const T* lam0, T* dL,
                                                                 int B, int q, int nf) {
   __shared__ double sh[WAVES][64];
-  const int r = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   constexpr int LG = GE == 8 ? 3 : GE == 4 ? 2 : GE == 2 ? 1 : 0;
   T w[FPL];
   double acc[FPL];
@@ -217,7 +221,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_open_grad_dense(const T* y, cons
     w[k] = f < nf ? L[(size_t)r * nf + f] : T(0);
     acc[k] = 0.0;
   }
-  T yn[GE][FPL], ln;
+  T yn[GE][FPL], ln;  // loads without a branch, past the end the last valid value again
   const int me = lane >> (6 - LG);  // the example whose z this lane ends up with
   auto fetch = [&](int e0) {
 #pragma unroll
@@ -225,36 +229,65 @@ __global__ __launch_bounds__(64 * WAVES) void k_open_grad_dense(const T* y, cons
 #pragma unroll
       for (int k = 0; k < FPL; ++k) {
         const int f = lane + 64 * k;
-        yn[i][k] = e0 + i < B && f < nf ? y[(size_t)(e0 + i) * nf + f] : T(0);
+        yn[i][k] = y[(size_t)min(e0 + i, B - 1) * nf + min(f, nf - 1)];
       }
-    ln = e0 + me < B ? lam0[(size_t)(e0 + me) * q + r] : T(0);
+    ln = lam0[(size_t)min(e0 + me, B - 1) * q + r];
   };
-  fetch(wave * GE);
-  for (int e0 = wave * GE; e0 < B; e0 += WAVES * GE) {
-    T v[GE][FPL], p[GE];
-    const T lam = ln;
+  // the sums of p[0 .. GE) over the lanes, that of example `me` in each lane
+  auto lane_sums = [&](T(&p)[GE]) {
 #pragma unroll
-    for (int i = 0; i < GE; ++i) {
-      p[i] = T(0);
-#pragma unroll
-      for (int k = 0; k < FPL; ++k) {
-        v[i][k] = yn[i][k];
-        p[i] = fma(w[k], v[i][k], p[i]);
-      }
-    }
-    fetch(e0 + WAVES * GE);
-    int off = 32;
-#pragma unroll
-    for (int n = GE; n > 1; n /= 2, off /= 2) {
+    for (int k = 0; k < LG; ++k) {
+      const int half = GE >> (k + 1), off = 32 >> k;
       const bool up = lane & off;
 #pragma unroll
-      for (int i = 0; i < n / 2; ++i) {
-        const T send = up ? p[i] : p[i + n / 2], keep = up ? p[i + n / 2] : p[i];
+      for (int i = 0; i < half; ++i) {
+        // (a choice between the array's elements themselves would index it at run time)
+        const T lo = p[i], hi = p[i + half], send = up ? lo : hi, keep = up ? hi : lo;
         p[i] = keep + __shfl_xor(send, off, 64);
       }
     }
-    for (; off > 0; off /= 2) p[0] += __shfl_xor(p[0], off, 64);
-    const T s = e0 + me < B ? dact_f<T, ACT>(p[0]) * lam : T(0);
+#pragma unroll
+    for (int k = LG; k < 6; ++k) p[0] += __shfl_xor(p[0], 32 >> k, 64);
+    return p[0];
+  };
+  fetch(wave * GE);
+  for (int e0 = wave * GE; e0 < B; e0 += WAVES * GE) {
+    T v[GE][FPL], p[GE], m[GE];
+    const T lam = ln;
+#pragma unroll
+    for (int i = 0; i < GE; ++i) {
+      p[i] = m[i] = T(0);
+#pragma unroll
+      for (int k = 0; k < FPL; ++k) {
+        v[i][k] = e0 + i < B && lane + 64 * k < nf ? yn[i][k] : T(0);
+        p[i] = fma(w[k], v[i][k], p[i]);
+        m[i] = fma(fabs(w[k]), fabs(v[i][k]), m[i]);  // ReLU only
+      }
+    }
+    fetch(e0 + WAVES * GE);
+    T z = lane_sums(p);
+    if constexpr (ACT == ACT_RELU) {
+      // each order's rounding: (nf + FPL + 6) / 2 eps sum |L y| together; first by a bound
+      // of the sum that takes no exchange, 64 times the largest lane's part
+      constexpr T eps = std::numeric_limits<T>::epsilon();
+      const int c = (nf + FPL + 8) >> 1;
+      const T zs = ldexp(fabs(z), std::numeric_limits<T>::digits - 1 - 6 - (32 - __builtin_clz(c)));
+      uint64_t any = 0;
+#pragma unroll
+      for (int i = 0; i < GE; ++i) any |= __ballot(lane_value(zs, i << (6 - LG)) < m[i]);
+      if (any) {
+        const uint64_t near = __ballot(fabs(z) < T(c) * eps * lane_sums(m));
+        for (int i = 0; i < GE; ++i) {
+          if (!(near >> (i << (6 - LG)) & 1)) continue;  // past B: 0 < 0
+          const T* yr = y + (size_t)(e0 + i) * nf;
+          T zi = T(0);
+#pragma unroll 8
+          for (int f = 0; f < nf; ++f) zi = fma(L[(size_t)r * nf + f], yr[f], zi);
+          z = me == i ? zi : z;
+        }
+      }
+    }
+    const T s = e0 + me < B ? dact_f<T, ACT>(z) * lam : T(0);
     T a[FPL];
 #pragma unroll
     for (int i = 0; i < GE; ++i) {
@@ -334,12 +367,14 @@ void open_grad_dense(const T* y, const T* L, const T* lam0, T* dL, int B, int q,
   const auto few = [&](auto n) {
     k_open_grad_few<T, ACT, decltype(n)::value><<<q, GNT, 0, st>>>(y, L, lam0, dL, B, q, nf);
   };
-  // about 64 registers of examples in flight per lane; from two features a lane on fp64
-  // takes half the waves, with twice the registers each (at 16 waves it spills: 1024
-  // features, 16384 examples, 32 rows 12.4 ms, 3.0 with 8)
+  // about 64 registers of examples in flight per lane; fp64 from two features a lane on
+  // and fp32 with 16 take half the waves, with twice the registers each (at 16 waves they
+  // spill: 1024 features, 16384 examples, 32 rows, tanh: fp64 12.4 ms, 3.1 with 8 waves;
+  // fp32 2.9 ms and 1.0)
   const auto run = [&](auto fpl) {
     constexpr int FPL = decltype(fpl)::value, W = FPL * (int)sizeof(T) / 4;
-    constexpr int GE = W <= 4 ? 8 : W <= 8 ? 4 : 2, WAVES = sizeof(T) == 8 && FPL > 1 ? 8 : 16;
+    constexpr int GE = W <= 4 ? 8 : W <= 8 ? 4 : W <= 16 ? 2 : 1;
+    constexpr int WAVES = W > 8 || (sizeof(T) == 8 && FPL > 1) ? 8 : 16;
     k_open_grad_dense<T, ACT, FPL, GE, WAVES><<<q, 64 * WAVES, 0, st>>>(y, L, lam0, dL, B, q, nf);
   };
   if (nf <= 2) few(std::integral_constant<int, 2>{});

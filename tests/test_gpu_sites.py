@@ -1,7 +1,8 @@
 """A ReLU site within rounding of zero is decided once: in the families that run split
 bf16 products (3x3 convolutions, width 220) every kernel that evaluates a layer forms
 its pre-activation with the same arithmetic, so the gradient that recomputes sigma'
-agrees bit for bit with the one that reads the solve's record."""
+agrees bit for bit with the one that reads the solve's record. The gradient of a dense
+opening decides its sites as the opening layer did."""
 import pytest
 import torch
 
@@ -60,3 +61,24 @@ def test_wide_gradient_decides_sites_as_the_solve():
         L.lp_gradient(p, K, b, U, Lam, dK, db, ws, dsig=r)
         out.append((dK, db))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+# an example per thread (nf <= 8), then 1, 2, 4, 8, 16 features per lane
+@pytest.mark.parametrize("dtype,nf", [("f32", 7), ("f32", 9), ("f32", 64), ("f32", 100), ("f32", 220), ("f32", 512),
+                                      ("f32", 1024), ("f64", 16), ("f64", 130)])
+def test_opening_gradient_decides_sites_as_the_layer(dtype, nf):
+    g = torch.Generator(device="cuda").manual_seed(5)
+    dt, B, q = {"f32": torch.float32, "f64": torch.float64}[dtype], 500, 8
+    p = L.problem(dtype, "dense", "relu", 1, B, q)
+    y, Lw, lam = (torch.randn(*s, generator=g, device="cuda", dtype=torch.float64).to(dt) for s in ((B, nf), (q, nf), (B, q)))
+    y[:, -1] = 0.0
+    y[:, -1] = (-(y.double() @ Lw[0].double()) / Lw[0, -1].double()).to(dt)  # the first row's z is zero to rounding
+    u0, dL = torch.empty(B, q, device="cuda", dtype=dt), torch.empty_like(Lw)
+    L.lp_open_forward(p, L.LP_OPEN_DENSE_ACT, nf, y, Lw, u0)
+    L.lp_open_grad(p, L.LP_OPEN_DENSE_ACT, nf, y, Lw, lam, dL)
+    assert 0.02 < float((u0[:, 0] > 0).double().mean()) < 0.98  # the sites are at zero
+    s = (u0 > 0).double() * lam.double()
+    ref, scale = s.T.contiguous() @ y.double(), s.abs().T.contiguous() @ y.double().abs()
+    # products and at most 8 terms at a time in the type, the rest in 64 bits (B terms)
+    bound = 16 * torch.finfo(dt).eps + B * 2.0 ** -52
+    assert float(((dL.double() - ref).abs() / (scale + 1e-300)).max()) <= bound
